@@ -104,6 +104,7 @@ hipError_t launch_staged_gemm(const TransferArgs& a, hipStream_t s);
 
 // Rows per workgroup tile of the transfer kernels.
 int transfer_rows_per_tile(int dtype, int H_r, int H_s, int n_taps, int d_h);
+int transfer_f32_rows_per_tile(int H_s, int n_taps, int d_h);
 // Device bytes of the staging record each row tile needs (0 where the kernel
 // that runs keeps no records), and the launch that writes the records
 // (a.tile_rec, one per tile of the batch) before launch_transfer.
@@ -118,6 +119,7 @@ hipError_t launch_rope_table(float* tab, int P, int d_h, double theta, hipStream
 hipError_t launch_pack_maps(int dtype, int n_lc, int d_r, int d_in, const void* A, void* A_packed,
                             hipStream_t s);
 hipError_t launch_transfer(int dtype, const TransferArgs& a, hipStream_t s);
+hipError_t launch_transfer_f32(const TransferArgs& a, hipStream_t s);
 // Device address of the no-allocation scratch (HF_NOALLOC_SCRATCH_BYTES) on the
 // current device; resolved once per device.
 hipError_t noalloc_scratch(void** ptr);

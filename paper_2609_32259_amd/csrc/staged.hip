@@ -16,8 +16,7 @@
 // one XCD (workgroup i runs on XCD i % 8), where they share the row tile in L2.
 #include <hip/hip_runtime.h>
 
-#include <cstddef>
-
+#include "hf_device.h"
 #include "hf_internal.h"
 
 namespace hf {
@@ -86,16 +85,6 @@ struct Job {
   uint16_t* rbase;        // receiver cache at (sequence, layer, role, head 2 nt, row 0)
   int nt, j0, Tr, pos0, keys, l;
 };
-
-// Byte i of a kernel-argument byte array, read as the aligned dword that holds
-// it: gfx950 has no scalar byte loads, and a vector load here would wait (in
-// order) for every load and store in flight.
-static_assert(offsetof(TransferArgs, taps) % 4 == 0, "taps must be dword aligned");
-FI int arg_byte(const uint8_t* base, int i) {
-  i = __builtin_amdgcn_readfirstlane(i);
-  const uint32_t w = reinterpret_cast<const uint32_t*>(base)[i >> 2];
-  return (int)((w >> (8 * (i & 3))) & 0xffu);
-}
 
 FI Job decode(const TransferArgs& p, int xcd, int jj) {
   Job J;

@@ -4,12 +4,12 @@
 // the epilogue, written straight into the receiver cache layout).
 #include <hip/hip_runtime.h>
 
-#include <cstddef>
 #include <limits.h>
 
 #include <mutex>
 #include <type_traits>
 
+#include "hf_device.h"
 #include "hf_internal.h"
 
 namespace hf {
@@ -107,29 +107,6 @@ __global__ __launch_bounds__(256) void copy_f32_kernel(const float4* A, float4* 
   if (idx < n4) Wp[idx] = A[idx];
 }
 
-// ---------------------------------------------------------------------------
-// Work decoding shared by the transfer kernels.  Work items run role-major,
-// then layer, then sequence, then row tile, so the workgroups in flight at
-// any time share one map A[l, c] (kept in L2) and the two sender layers it
-// reads, and consecutive receiver layers reuse a sender layer.
-// ---------------------------------------------------------------------------
-struct Item {
-  int c, l, b, tile;
-};
-
-__device__ __forceinline__ Item decode_item(const TransferArgs& p, int item) {
-  Item it;
-  const int lc = item / p.tiles_per_lc;
-  int t = item - lc * p.tiles_per_lc;
-  it.c = lc / p.L_r;
-  it.l = lc - it.c * p.L_r;
-  int b = 0;
-  while (b + 1 < p.B && p.tile_start[b + 1] <= t) ++b;
-  it.b = b;
-  it.tile = t - p.tile_start[b];
-  return it;
-}
-
 constexpr int kDH = 128;
 constexpr int kXS = kDH + 8;  // LDS row stride of X / staging, bf16 elements (16-byte pad)
 
@@ -142,19 +119,6 @@ struct Ctx {
   bool two_tap;
   int Ts;
 };
-
-// Byte i of a kernel-argument byte array (lo, hi, taps), read as the aligned
-// dword that holds it with a uniform index: gfx950 has no scalar byte loads,
-// and a vector load here would wait (in order) for every load and store the
-// workgroup still has in flight, such as the previous tile's receiver rows.
-static_assert(offsetof(TransferArgs, lo) % 4 == 0 && offsetof(TransferArgs, hi) % 4 == 0 &&
-                  offsetof(TransferArgs, taps) % 4 == 0,
-              "layer-map byte arrays must be dword aligned");
-__device__ __forceinline__ int arg_byte(const uint8_t* base, int i) {
-  i = __builtin_amdgcn_readfirstlane(i);
-  const uint32_t w = reinterpret_cast<const uint32_t*>(base)[i >> 2];
-  return (int)((w >> (8 * (i & 3))) & 0xffu);
-}
 
 // Tap t of the layer map: with concatenated taps, sender layer taps[l][t]
 // with weight 1; otherwise (t = 0) the interpolation of lo and hi.
@@ -1146,135 +1110,12 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_direct_kernel(const Tran
                      j0 + 64 * wm + 32 * mt, Tr, lane);
 }
 
-// ---------------------------------------------------------------------------
-// fp32 transfer kernel: the same definitions with fp32 operands and plain
-// FMA, any even d_h.  One workgroup = RT receiver rows of one (layer, role).
-// ---------------------------------------------------------------------------
-constexpr int kF32Threads = 256;
-
-__global__ __launch_bounds__(kF32Threads) void transfer_f32_kernel(const TransferArgs p) {
-  extern __shared__ float xs[];  // [RT][d_in]
-  const Item it = decode_item(p, blockIdx.x);
-  const int RT = p.rows_per_tile;
-  const int d = p.d_h, half = d / 2;
-  const int NV = p.n_taps * p.H_s;  // (tap, sender head) blocks of the map row
-  const int d_in = NV * d, d_r = p.H_r * d;
-  const int j0 = it.tile * RT;
-  const int Tr = p.Tr[it.b], Ts = p.Ts[it.b];
-  const bool keys = it.c == 0;
-  const bool unrot = keys && p.unrot, rot = keys && p.rot;
-  const float sr = p.inv_r ? p.inv_r[it.l * 2 + it.c] : 1.0f;  // the map sees x / r
-  const float wlo = p.wlo[it.l] * sr, whi = p.whi[it.l] * sr;
-  const bool two_tap = p.whi[it.l] != 0.0f;
-  const float* Sb = static_cast<const float*>(p.S) + it.b * p.s_sb + it.c * p.s_sc;
-  const int lc_store = it.l * 2 + it.c;
-
-  for (int idx = threadIdx.x; idx < RT * NV * half; idx += kF32Threads) {
-    const int r = idx / (NV * half);
-    const int rem = idx - r * (NV * half);
-    const int vh = rem / half, f = rem - vh * half;
-    const int h = vh % p.H_s, t = vh / p.H_s;
-    const int lo = p.concat ? p.taps[it.l][t] : p.lo[it.l];
-    const float* S_lo = Sb + (long long)lo * p.s_sl;
-    const float* S_hi = Sb + (long long)(p.concat ? lo : p.hi[it.l]) * p.s_sl;
-    const int j = j0 + r;
-    float x1 = 0.f, x2 = 0.f;
-    if (j < Tr) {
-      const int g = p.row0[it.b] + j;
-      const float dinv = (float)p.den[g];
-      for (int e = p.row_ptr[g]; e < p.row_ptr[g + 1]; ++e) {
-        int i = min(max(p.col[e], 0), Ts - 1);
-        const float w = (float)p.num[e] / dinv;
-        const long long off = h * p.s_sh + (long long)i * p.s_st + f;
-        float m1 = wlo * S_lo[off], m2 = wlo * S_lo[off + half];
-        if (two_tap) {
-          m1 = fmaf(whi, S_hi[off], m1);
-          m2 = fmaf(whi, S_hi[off + half], m2);
-        }
-        if (unrot) {
-          const float* cs = p.cs_s + (long long)(p.pos0_s[it.b] + i) * d;
-          const float c = cs[f], s = cs[half + f];
-          const float u1 = fmaf(m1, c, m2 * s);
-          const float u2 = fmaf(m2, c, -m1 * s);
-          m1 = u1;
-          m2 = u2;
-        }
-        x1 = fmaf(w, m1, x1);
-        x2 = fmaf(w, m2, x2);
-      }
-    }
-    xs[r * d_in + vh * d + f] = x1;
-    xs[r * d_in + vh * d + f + half] = x2;
-  }
-  __syncthreads();
-
-  const float* W = static_cast<const float*>(p.Wp) + (long long)lc_store * d_r * d_in;
-  float* Rb = static_cast<float*>(p.R) + it.b * p.r_sb + (long long)it.l * p.r_sl + it.c * p.r_sc;
-  constexpr int kMaxRT = 16;
-  const float* knorm = (keys && p.k_norm) ? p.k_norm + (long long)it.l * d : nullptr;
-  // Every thread takes the same number of trips (pc past the end computes
-  // nothing and stores nothing), so the key norm's shuffles see whole waves;
-  // the half = d/2 threads of one receiver head are consecutive lanes.
-  for (int pc0 = 0; pc0 < p.H_r * half; pc0 += kF32Threads) {
-    const int pc = pc0 + threadIdx.x;
-    const bool live = pc < p.H_r * half;
-    const int hr = live ? pc / half : 0, f = live ? pc - hr * half : 0;
-    const int n1 = hr * d + f, n2 = n1 + half;
-    float y1[kMaxRT], y2[kMaxRT];
-#pragma unroll
-    for (int r = 0; r < kMaxRT; ++r) y1[r] = y2[r] = 0.f;
-    const float* W1 = W + (long long)n1 * d_in;
-    const float* W2 = W + (long long)n2 * d_in;
-    for (int k = 0; k < (live ? d_in : 0); ++k) {
-      const float a1 = W1[k], a2 = W2[k];
-#pragma unroll
-      for (int r = 0; r < kMaxRT; ++r) {
-        if (r < RT) {
-          const float xv = xs[r * d_in + k];
-          y1[r] = fmaf(a1, xv, y1[r]);
-          y2[r] = fmaf(a2, xv, y2[r]);
-        }
-      }
-    }
-    const float b1 = (p.bias && live) ? p.bias[(long long)lc_store * d_r + n1] : 0.f;
-    const float b2 = (p.bias && live) ? p.bias[(long long)lc_store * d_r + n2] : 0.f;
-    const float g1 = knorm ? knorm[f] : 1.f, g2 = knorm ? knorm[f + half] : 1.f;
-#pragma unroll
-    for (int r = 0; r < kMaxRT; ++r) {
-      const int j = j0 + r;
-      if (r >= RT) continue;  // uniform: the shuffles below stay whole-wave
-      float v1 = y1[r] + b1, v2 = y2[r] + b2;
-      if (knorm) {  // RMSNorm over the head's d features, held by half lanes
-        float ss = fmaf(v1, v1, v2 * v2);
-        for (int o = 1; o < half; o <<= 1) ss += __shfl_xor(ss, o);
-        const float inv = 1.0f / sqrtf(ss / (float)d + p.k_norm_eps);
-        v1 *= inv * g1;
-        v2 *= inv * g2;
-      }
-      if (!live || j >= Tr) continue;
-      if (rot) {
-        const float* cs = p.cs_r + (long long)(p.pos0_r[it.b] + j) * d;
-        const float c = cs[f], s = cs[half + f];
-        const float u1 = fmaf(v1, c, -v2 * s);
-        const float u2 = fmaf(v2, c, v1 * s);
-        v1 = u1;
-        v2 = u2;
-      }
-      float* dst = Rb + hr * p.r_sh + (long long)j * p.r_st;
-      dst[f] = v1;
-      dst[f + half] = v2;
-    }
-  }
-}
-
 }  // namespace
 
 int transfer_rows_per_tile(int dtype, int H_r, int H_s, int n_taps, int d_h) {
   if (dtype == HF_BF16)
     return ((H_r == 4 || H_r == 8) && H_s <= kHMax) ? 64 : 64 * (8 / (H_r > 0 ? H_r : 1));
-  const int d_in = n_taps * H_s * d_h;
-  int rt = 8192 / (d_in > 0 ? d_in : 1);  // fp32 X tile <= 32 KB of LDS
-  return rt < 1 ? 1 : (rt > 16 ? 16 : rt);
+  return transfer_f32_rows_per_tile(H_s, n_taps, d_h);
 }
 
 static bool uses_tiled(int dtype, int H_r, int H_s, int d_h) {
@@ -1398,8 +1239,7 @@ hipError_t launch_transfer(int dtype, const TransferArgs& a, hipStream_t s) {
       default: return hipErrorInvalidValue;
     }
   } else {
-    const size_t shmem = (size_t)a.rows_per_tile * a.n_taps * a.H_s * a.d_h * sizeof(float);
-    hipLaunchKernelGGL(transfer_f32_kernel, grid, dim3(kF32Threads), shmem, s, a);
+    return launch_transfer_f32(a, s);
   }
   return hipGetLastError();
 }
