@@ -193,13 +193,6 @@ __device__ __forceinline__ void build_row_global(const TransferArgs& p, const Ct
   }
 }
 
-// 1 / sqrt(mean(y^2) + eps) of one receiver head row of 128 features whose
-// squares are split between this lane (ss) and lane ^ 32.
-__device__ __forceinline__ float rms_scale_pair(float ss, float eps) {
-  ss += __shfl_xor(ss, 32);
-  return 1.0f / sqrtf(ss * (1.0f / kDH) + eps);
-}
-
 // y[q][4 g + u] *= inv * weight of its feature feat[q] + 8 g + hi4 + u.
 template <int NTW>
 __device__ __forceinline__ void scale_by_weights(float (*y)[16], const int* feat, int hi4,
@@ -214,82 +207,6 @@ __device__ __forceinline__ void scale_by_weights(float (*y)[16], const int* feat
       y[q][4 * g + 2] *= inv * w.z;
       y[q][4 * g + 3] *= inv * w.w;
     }
-}
-
-// Epilogue of one 32-row block of a wave: bias, receiver RoPE on keys, bf16
-// rounding, then a write through the wave's LDS staging rows so that global
-// stores cover whole contiguous row segments.
-//   acc[q]  accumulators of the wave's n-tile q (NTW of them) for these rows;
-//   feat[q] first feature (within the receiver head) of n-tile q;
-//   tiles q and q + NTW/2 hold the RoPE pair (f, f + 64).
-template <int NTW>
-__device__ __forceinline__ void epilogue_rows(const TransferArgs& p, f32x16* acc, const int* feat,
-                                              const float* bias_head, const float* cr, bool rot,
-                                              const float* knorm, uint16_t* stage,
-                                              uint16_t* dst_head, int row_base, int Tr, int lane) {
-  static_assert(NTW == 4, "the key norm needs the whole head in the wave");
-  const int hi4 = 4 * (lane >> 5);
-  const int mcol = lane & 31;
-  const int j = row_base + mcol;
-  float y[NTW][16];
-#pragma unroll
-  for (int q = 0; q < NTW; ++q)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (bias_head) bv = *reinterpret_cast<const float4*>(bias_head + feat[q] + 8 * g + hi4);
-      y[q][4 * g + 0] = acc[q][4 * g + 0] + bv.x;
-      y[q][4 * g + 1] = acc[q][4 * g + 1] + bv.y;
-      y[q][4 * g + 2] = acc[q][4 * g + 2] + bv.z;
-      y[q][4 * g + 3] = acc[q][4 * g + 3] + bv.w;
-    }
-  if (knorm) {  // receiver key RMSNorm over the head's 128 features (lanes l, l ^ 32)
-    float ss = 0.0f;
-#pragma unroll
-    for (int q = 0; q < NTW; ++q)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) ss = fmaf(y[q][i], y[q][i], ss);
-    scale_by_weights<NTW>(y, feat, hi4, knorm, rms_scale_pair(ss, p.k_norm_eps));
-  }
-  if (rot && j < Tr) {
-    const float* crow = cr + (long long)j * kDH;
-#pragma unroll
-    for (int q = 0; q < NTW / 2; ++q)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int f = feat[q] + 8 * g + hi4;  // < 64
-        const float4 cv = *reinterpret_cast<const float4*>(crow + f);
-        const float4 sv = *reinterpret_cast<const float4*>(crow + 64 + f);
-        const float cc[4] = {cv.x, cv.y, cv.z, cv.w};
-        const float ss[4] = {sv.x, sv.y, sv.z, sv.w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float a = y[q][4 * g + u], b = y[q + NTW / 2][4 * g + u];
-          y[q][4 * g + u] = fmaf(a, cc[u], -b * ss[u]);
-          y[q + NTW / 2][4 * g + u] = fmaf(b, cc[u], a * ss[u]);
-        }
-      }
-  }
-  // stage row mcol: tile q occupies staging columns [32 q, 32 q + 32)
-#pragma unroll
-  for (int q = 0; q < NTW; ++q)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint2 v = make_uint2(pack2(y[q][4 * g], y[q][4 * g + 1]), pack2(y[q][4 * g + 2], y[q][4 * g + 3]));
-      *reinterpret_cast<uint2*>(stage + mcol * kXS + 32 * q + 8 * g + hi4) = v;
-    }
-  // write back: NTW*4 lanes per row, each 16 bytes
-  constexpr int LPR = NTW * 4;
-  constexpr int RPP = 64 / LPR;
-#pragma unroll
-  for (int pass = 0; pass < 32 / RPP; ++pass) {
-    const int rr = pass * RPP + lane / LPR;
-    const int ci = lane % LPR;
-    const uint4 v = *reinterpret_cast<const uint4*>(stage + rr * kXS + 8 * ci);
-    const int jj = row_base + rr;
-    if (jj < Tr)
-      *reinterpret_cast<uint4*>(dst_head + (long long)jj * p.r_st + feat[ci / 4] + 8 * (ci % 4)) = v;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -406,8 +323,8 @@ struct LdsSink {  // the X tile in LDS (row stride kXF)
 
 template <bool TWO_TAP, bool UNROT, int R, class Sink>
 __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& p, const GroupLds& L,
-                                             int base, int head, int r_first, int rpg, int lane,
-                                             const Sink& sink) {
+                                             int base, int src_head, int head, int r_first, int rpg,
+                                             int lane, const Sink& sink) {
   const int e0 = (lane & 7) * 8;
   const int kb = L.estart[r_first] - L.e_base;
   const int E = L.estart[r_first + rpg] - L.e_base - kb;
@@ -437,7 +354,7 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
       __builtin_amdgcn_make_buffer_rsrc((void*)cx.S_lo, 0, p.s_extent, 0x00020000);
   const __amdgpu_buffer_rsrc_t rhi =
       __builtin_amdgcn_make_buffer_rsrc((void*)cx.S_hi, 0, p.s_extent, 0x00020000);
-  const int hoff = (int)(head * p.s_sh + e0) * 2;  // bytes
+  const int hoff = (int)(src_head * p.s_sh + e0) * 2;  // bytes
   const int tstride = (int)p.s_st * 2;
 
   Trip<TWO_TAP> ring[R];
@@ -529,9 +446,8 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
 // rotation table), [1] the tile has more than kEMax entries.  Every (layer,
 // role) of the tile reads the same record.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(512) void stage_tiles_kernel(const TransferArgs p, int* rec) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p.work_ctr = p.n_wg;  // items [0, n_wg) start statically
-  __shared__ __attribute__((aligned(16))) int ent[kRecBytes / 4];
+// Tile t's record into ent (LDS), by 512 threads.
+__device__ __forceinline__ void stage_tile(const TransferArgs& p, int t, int* ent) {
   int* estart = ent;
   int* gbase = estart + 65;
   int* ecol = gbase + 64;
@@ -542,7 +458,6 @@ __global__ __launch_bounds__(512) void stage_tiles_kernel(const TransferArgs p, 
   int* rmin = gstart + 65;    // smallest / largest sender index of each tile row
   int* rmax = rmin + 64;
 
-  const int t = blockIdx.x;
   int b = 0;
   while (b + 1 < p.B && p.tile_start[b + 1] <= t) ++b;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -611,12 +526,24 @@ __global__ __launch_bounds__(512) void stage_tiles_kernel(const TransferArgs p, 
     if (lane == 0 && !fits) flag[1] = 1;
   }
   __syncthreads();
-  int4* dst = reinterpret_cast<int4*>(rec + (long long)t * (kRecBytes / 4));
-  dst[tid] = reinterpret_cast<const int4*>(ent)[tid];
 }
 
-template <int NTW, bool MULTI>
+__global__ __launch_bounds__(512) void stage_tiles_kernel(const TransferArgs p, int* rec) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *p.work_ctr = p.n_wg;  // items [0, n_wg) start statically
+  __shared__ __attribute__((aligned(16))) int ent[kRecBytes / 4];
+  stage_tile(p, blockIdx.x, ent);
+  int4* dst = reinterpret_cast<int4*>(rec + (long long)blockIdx.x * (kRecBytes / 4));
+  dst[threadIdx.x] = reinterpret_cast<const int4*>(ent)[threadIdx.x];
+}
+
+// HR: receiver heads.  MULTI: several passes over the X tile (concatenated taps,
+// or more than kHMax sender heads).  OWN: the call's workspace has no records
+// and no work counter (two receiver heads, or more than kHMax sender heads), so
+// every workgroup does one item and stages its tile itself.
+template <int HR, bool MULTI, bool OWN>
 __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const TransferArgs p) {
+  constexpr int NTW = HR == 8 ? 4 : 2;  // 32-feature tiles per wave
+  constexpr int MT = HR == 2 ? 1 : 2;   // 32-row blocks per wave
   __shared__ __attribute__((aligned(16))) unsigned char smem[kSmemBytes];
   uint16_t* Xs = reinterpret_cast<uint16_t*>(smem);
   float* dt = reinterpret_cast<float*>(smem + kOffDt);
@@ -647,9 +574,10 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   // contiguous run of the work order, and the next record is copied in during
   // the store.  With concatenated taps (whose per-tap passes leave no registers
   // for the loop) a workgroup does the one item blockIdx.x.
-  constexpr bool kPersist = !MULTI;
+  constexpr bool kPersist = !MULTI && !OWN;
   int item = blockIdx.x;
-  copy_record(item);
+  if (OWN) stage_tile(p, item % p.tiles_per_lc, estart);
+  else copy_record(item);
   if (p.unrot) {  // U(0..15): rows 0..15 of the sender table, 2 per wave
     const int ri = wave * 2 + (lane >> 5);
     const int c = (lane & 31) ^ (ri & 1);
@@ -671,71 +599,86 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   int grabbed = n_items;
   if (kPersist && tid == 0) grabbed = atomicAdd(p.work_ctr, 1);
 
-  f32x16 acc[2][NTW];  // zeroed after the first tap's build
+  f32x16 acc[MT][NTW];  // zeroed after the first pass's build
   // This wave's accumulators: receiver head `head`, n-tiles feat[q].
-  const int head = NTW == 4 ? wave : (wave >> 1);
-  const int nt0 = NTW == 4 ? 0 : (wave & 1);
+  const int head = HR == 8 ? wave : HR == 4 ? (wave >> 1) : (wave >> 2);
+  const int nt0 = HR == 8 ? 0 : HR == 4 ? (wave & 1) : ((wave >> 1) & 1);
+  const int row0 = HR == 2 ? 32 * (wave & 1) : 0;  // the wave's first tile row
   constexpr int NTS = 4 / NTW;  // n-tile stride inside the head
   int feat[NTW];
 #pragma unroll
   for (int q = 0; q < NTW; ++q) feat[q] = 32 * (nt0 + q * NTS);
-  const int KS = H * (kDH / 16);  // k-steps of one tap
   const int NB = p.H_r * (kDH / 32);
   const int lc_store = it.l * 2 + it.c;
-  const int ks0 = (int)((unsigned)item % (unsigned)H) * (kDH / 16);  // this item's first k-step
 
-  // One pass per tap of the layer map (MULTI: concatenated taps, each one
-  // sender layer): build that tap's X, multiply it by the matching k block of
-  // the map into the same accumulators.  From the second tap on the
+  // One pass per tap of the layer map (concatenated taps, each one sender layer)
+  // and group of kHMax sender heads: build its X, multiply it by the matching k
+  // block of the map into the same accumulators.  From the second pass on the
   // accumulators are live during the build, which then keeps fewer loads in
   // flight.
-  const int n_pass = MULTI ? p.n_taps : 1;
-  for (int tap = 0; tap < n_pass; ++tap) {
-    if (tap > 0) __syncthreads();  // every wave is done reading the previous tap's X
+  const int n_grp = OWN ? (H + kHMax - 1) / kHMax : 1;
+  const int n_pass = MULTI ? p.n_taps * n_grp : 1;
+  for (int pass = 0; pass < n_pass; ++pass) {
+    if (pass > 0) __syncthreads();  // every wave is done reading the previous pass's X
+    const int tap = pass / n_grp, h_first = OWN ? kHMax * (pass - tap * n_grp) : 0;
+    const int Hp = OWN ? min(kHMax, H - h_first) : H;  // sender heads of this pass
+    const int KS = Hp * (kDH / 16);                    // and its k-steps
+    const int ks0 = (int)((unsigned)item % (unsigned)Hp) * (kDH / 16);  // the first one
     const Ctx ct = make_ctx(p, it, tap);
-    // ---- build X[64][d_in] of this tap ----
+    // ---- build X[64][Hp d_h] of this pass ----
     if (staged) {
       const LdsSink xsink{Xs};
       const int sh = wave / WPH;  // sender head this wave builds
-      if (sh < H) {
+      if (sh < Hp) {
         const GroupLds L{estart, ecol, ew, einfo, dt, e_base};
         const int grp = (wave % WPH) * 8 + (lane >> 3);
         const int r_first = gstart[grp];
         const int rpg = gstart[grp + 1] - r_first;
         const int base = gbase[grp];
-        if (MULTI) {  // one sender layer per tap
-          if (tap == 0) {
-            if (unrot) build_groups<false, true, 3>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
-            else build_groups<false, false, 3>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
+        const int src = h_first + sh;
+        auto build = [&](auto two, auto rotate, auto ring) {
+          build_groups<decltype(two)::value, decltype(rotate)::value, decltype(ring)::value>(
+              ct, p, L, base, src, sh, r_first, rpg, lane, xsink);
+        };
+        using T = std::true_type;
+        using F = std::false_type;
+        using R3 = std::integral_constant<int, 3>;
+        using R2 = std::integral_constant<int, 2>;
+        // two receiver heads leave registers for the deeper ring in every pass
+        using Rn = std::conditional_t<HR == 2, R3, R2>;
+        if ((!MULTI || OWN) && ct.two_tap) {  // concatenated taps are one sender layer each
+          if (!MULTI || pass == 0) {
+            if (unrot) build(T(), T(), R3());
+            else build(T(), F(), R3());
           } else {
-            if (unrot) build_groups<false, true, 2>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
-            else build_groups<false, false, 2>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
+            if (unrot) build(T(), T(), Rn());
+            else build(T(), F(), Rn());
           }
-        } else if (ct.two_tap) {
-          if (unrot) build_groups<true, true, 3>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
-          else build_groups<true, false, 3>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
+        } else if (!MULTI || pass == 0) {
+          if (unrot) build(F(), T(), R3());
+          else build(F(), F(), R3());
         } else {
-          if (unrot) build_groups<false, true, 3>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
-          else build_groups<false, false, 3>(ct, p, L, base, sh, r_first, rpg, lane, xsink);
+          if (unrot) build(F(), T(), Rn());
+          else build(F(), F(), Rn());
         }
       }
     } else {
       const int r = tid >> 3;         // 8 threads per row
       const int e0 = (tid & 7) * 8;   // features e0..e0+7 and e0+64..e0+71 of every head
-      for (int h = 0; h < H; ++h) {
+      for (int h = 0; h < Hp; ++h) {
         float x[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) x[u] = 0.0f;
-        if (r < nrows) build_row_global(p, ct, g0 + r, h, e0, x);
+        if (r < nrows) build_row_global(p, ct, g0 + r, h_first + h, e0, x);
         uint16_t* xr = Xs + r * kXF + h * kDH;
         *reinterpret_cast<uint4*>(xr + e0) = pack8(x);
         *reinterpret_cast<uint4*>(xr + 64 + e0) = pack8(x + 8);
       }
     }
     __syncthreads();
-    if (tap == 0) {
+    if (pass == 0) {
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int q = 0; q < NTW; ++q)
 #pragma unroll
@@ -743,44 +686,48 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
     }
 
     // ---- multiply ----
-    // The map block of this (layer, role, tap) through a buffer resource: a
+    // The map block of this (layer, role, pass) through a buffer resource: a
     // 32-bit per-lane offset plus the k-step's scalar offset, so a refill costs
     // no 64-bit address arithmetic.
     const bf16x8* Wblk =
-        static_cast<const bf16x8*>(p.Wp) + ((long long)lc_store * p.n_taps + tap) * KS * NB * 64;
+        static_cast<const bf16x8*>(p.Wp) +
+        (((long long)lc_store * p.n_taps + tap) * H + h_first) * (kDH / 16) * NB * 64;
     const __amdgpu_buffer_rsrc_t rW =
         __builtin_amdgcn_make_buffer_rsrc((void*)Wblk, 0, KS * NB * 64 * 16, 0x00020000);
     const int w_lane = ((4 * head + nt0) * 64 + lane) * 16;  // bytes within a k-step
-    bf16x8 wr[4][NTW];  // map fragments of four consecutive k-steps
+    // Map fragments of four consecutive k-steps, kept as integers: as bf16 vectors
+    // the compiler copied the first slot through registers and waited for
+    // every load in flight once per four k-steps (2.5% of a 4-head transfer).
+    u32x4 wr[4][NTW];
     auto kstep = [&](int ks) { int k = ks + ks0; return k >= KS ? k - KS : k; };
-    auto load_w = [&](bf16x8* dst, int ks) {
+    auto load_w = [&](u32x4* dst, int ks) {
       const int k_off = kstep(ks) * NB * 64 * 16;
 #pragma unroll
       for (int q = 0; q < NTW; ++q)
-        dst[q] = __builtin_bit_cast(
-            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rW, w_lane + q * NTS * 64 * 16, k_off, 0));
+        dst[q] = __builtin_amdgcn_raw_buffer_load_b128(rW, w_lane + q * NTS * 64 * 16, k_off, 0);
     };
     auto read_x = [&](bf16x8* xa, int ks) {
       const int k = kstep(ks);
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-        xa[mt] = *reinterpret_cast<const bf16x8*>(Xs + (32 * mt + (lane & 31)) * kXF + 16 * k +
+      for (int mt = 0; mt < MT; ++mt)
+        xa[mt] = *reinterpret_cast<const bf16x8*>(Xs + (row0 + 32 * mt + (lane & 31)) * kXF + 16 * k +
                                                 8 * (lane >> 5));
     };
-    bf16x8 xc[2], xn[2];  // X fragments of this k-step and the next
+    bf16x8 xc[MT], xn[MT];  // X fragments of this k-step and the next
     // One k-step: read next X from LDS, multiply, then refill this map slot with
     // k-step ks + 4.  LOAD is a constant so that the loop body has no branches
     // and every wait on a map fragment keeps the three younger k-steps in flight.
-    auto step = [&](bf16x8* wf, int ks, auto load) {
+    auto step = [&](u32x4* wf, int ks, auto load) {
       read_x(xn, ks + 1);
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int q = 0; q < NTW; ++q)
-          acc[mt][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[q], xc[mt], acc[mt][q], 0, 0, 0);
+          acc[mt][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[q]), xc[mt],
+                                                               acc[mt][q], 0, 0, 0);
       if (decltype(load)::value) load_w(wf, ks + 4);
-      xc[0] = xn[0];
-      xc[1] = xn[1];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) xc[mt] = xn[mt];
       __builtin_amdgcn_sched_barrier(0);  // keep the refill in this k-step
     };
     using Load = std::true_type;
@@ -832,8 +779,8 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   const int hi4 = 4 * (lane >> 5);
   const int mcol = lane & 31;
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    const int rl = 32 * mt + mcol;  // tile row held by this lane
+  for (int mt = 0; mt < MT; ++mt) {
+    const int rl = row0 + 32 * mt + mcol;  // tile row held by this lane
     float y[NTW][16];
 #pragma unroll
     for (int q = 0; q < NTW; ++q)
@@ -853,10 +800,10 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
 #pragma unroll
         for (int i = 0; i < 16; ++i) ss = fmaf(y[q][i], y[q][i], ss);
       ss += __shfl_xor(ss, 32);  // lane ^ 32 holds the same row's other features
-      if (NTW == 2) {            // the other half of the head sits in wave ^ 1
+      if (NTW == 2) {            // another wave holds the other half of the head
         rsum[wave * 32 + mcol] = ss;
         __syncthreads();
-        ss += rsum[(wave ^ 1) * 32 + mcol];
+        ss += rsum[(wave ^ (HR == 2 ? 2 : 1)) * 32 + mcol];
         __syncthreads();
       }
       const float inv = 1.0f / sqrtf(ss * (1.0f / kDH) + p.k_norm_eps);
@@ -895,7 +842,7 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
       const int rr = pass * RPP + lane / LPR;
       const int ci = lane % LPR;
       const uint4 v = *reinterpret_cast<const uint4*>(stage + rr * kXS + 8 * ci);
-      const int jj = j0 + 32 * mt + rr;
+      const int jj = j0 + row0 + 32 * mt + rr;
       if (jj < Tr)  // streaming store: the receiver rows are not read again here, so
                     // they should not push the shared map out of L2
         __builtin_nontemporal_store(
@@ -988,10 +935,10 @@ __global__ __launch_bounds__(512) void staged_build_kernel(const TransferArgs p)
     const GroupLds L{estart, ecol, ew, einfo, dt, estart[0]};
     const int grp = lane >> 3;
     const int r_first = gstart[grp], rpg = gstart[grp + 1] - r_first, base = gbase[grp];
-    if (cx.two_tap && unrot) build_groups<true, true, 3>(cx, p, L, base, wave, r_first, rpg, lane, sink);
-    else if (cx.two_tap) build_groups<true, false, 3>(cx, p, L, base, wave, r_first, rpg, lane, sink);
-    else if (unrot) build_groups<false, true, 3>(cx, p, L, base, wave, r_first, rpg, lane, sink);
-    else build_groups<false, false, 3>(cx, p, L, base, wave, r_first, rpg, lane, sink);
+    if (cx.two_tap && unrot) build_groups<true, true, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    else if (cx.two_tap) build_groups<true, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    else if (unrot) build_groups<false, true, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    else build_groups<false, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
     // The wave's own head (k-tiles 4 wave .. 4 wave + 3 of the 64 rows) goes
     // out as soon as its walk ends: LDS operations of one wave run in order.
     const int c8 = (lane & 3) * 8;
@@ -1019,111 +966,20 @@ __global__ __launch_bounds__(512) void staged_build_kernel(const TransferArgs p)
   }
 }
 
-// ---------------------------------------------------------------------------
-// bf16 transfer kernel, direct (d_h = 128, WN receiver heads): the same
-// computation with X built straight from global memory and one workgroup per
-// 64 (8/WN) rows.  Used for two receiver heads, where a 64-row tile over 8
-// waves would split a RoPE pair across lanes.
-// ---------------------------------------------------------------------------
-template <int WN>
-__global__ __launch_bounds__(512, 1) void transfer_bf16_direct_kernel(const TransferArgs p) {
-  constexpr int WM = 8 / WN;
-  constexpr int MT = 64 * WM;
-  constexpr int XBUF = MT * kXS;
-  constexpr int STAGE = 32 * kXS;
-  constexpr int LDS = (2 * XBUF > 8 * STAGE) ? 2 * XBUF : 8 * STAGE;
-  __shared__ __attribute__((aligned(16))) uint16_t lds[LDS];
-
-  const Item it = decode_item(p, blockIdx.x);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int j0 = it.tile * MT;
-  const int Tr = p.Tr[it.b];
-  const int row0 = p.row0[it.b];
-  const int KS = p.n_taps * p.H_s * (kDH / 16);  // k-steps of the whole map row
-  const int NB = p.H_r * (kDH / 32);
-  const int lc_store = it.l * 2 + it.c;
-  // Map fragments through a buffer resource over this (layer, role)'s block.
-  const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(static_cast<const bf16x8*>(p.Wp) + (long long)lc_store * KS * NB * 64), 0,
-      KS * NB * 64 * 16, 0x00020000);
-  const int w_lane = ((wn * 4) * 64 + lane) * 16;  // bytes
-  const int brow = tid >> 3;
-  const int e0 = (tid & 7) * 8;
-
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.0f;
-
-  // v runs over (tap, sender head) pairs: the k blocks of the map row
-  for (int v = 0; v < p.n_taps * p.H_s; ++v) {
-    const int h = v % p.H_s;
-    const Ctx cx = make_ctx(p, it, v / p.H_s);
-    uint16_t* xb = lds + (v & 1) * XBUF;
-#pragma unroll
-    for (int q = 0; q < WM; ++q) {
-      const int r = brow + 64 * q;
-      float x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = 0.0f;
-      if (j0 + r < Tr) build_row_global(p, cx, row0 + j0 + r, h, e0, x);
-      *reinterpret_cast<uint4*>(xb + r * kXS + e0) = pack8(x);
-      *reinterpret_cast<uint4*>(xb + r * kXS + e0 + 64) = pack8(x + 8);
-    }
-    __syncthreads();
-    const int v_off = v * 8 * NB * 64 * 16;  // k-steps of block v
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      bf16x8 xa[2], wf[4];
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-        xa[mt] = *reinterpret_cast<const bf16x8*>(
-            xb + (64 * wm + 32 * mt + (lane & 31)) * kXS + 16 * s + 8 * (lane >> 5));
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        wf[nt] = __builtin_bit_cast(
-            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rW, w_lane + (s * NB + nt) * 64 * 16, v_off, 0));
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[nt], xa[mt], acc[mt][nt], 0, 0, 0);
-    }
-  }
-  __syncthreads();  // every wave is done reading X; LDS becomes staging space
-
-  const int feat[4] = {0, 32, 64, 96};
-  uint16_t* stage = lds + wave * STAGE;
-  uint16_t* dst_head = static_cast<uint16_t*>(p.R) + it.b * p.r_sb + (long long)it.l * p.r_sl +
-                       it.c * p.r_sc + wn * p.r_sh;
-  const float* bias_head = p.bias ? p.bias + (long long)lc_store * NB * 32 + wn * kDH : nullptr;
-  const bool rot = it.c == 0 && p.rot;
-  const float* cr = rot ? p.cs_r + (long long)p.pos0_r[it.b] * kDH : nullptr;
-  const float* knorm = (it.c == 0 && p.k_norm) ? p.k_norm + (long long)it.l * kDH : nullptr;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-    epilogue_rows<4>(p, acc[mt], feat, bias_head, cr, rot, knorm, stage, dst_head,
-                     j0 + 64 * wm + 32 * mt, Tr, lane);
-}
-
 }  // namespace
 
 int transfer_rows_per_tile(int dtype, int H_r, int H_s, int n_taps, int d_h) {
-  if (dtype == HF_BF16)
-    return ((H_r == 4 || H_r == 8) && H_s <= kHMax) ? 64 : 64 * (8 / (H_r > 0 ? H_r : 1));
+  if (dtype == HF_BF16) return 64;
   return transfer_f32_rows_per_tile(H_s, n_taps, d_h);
 }
 
-static bool uses_tiled(int dtype, int H_r, int H_s, int d_h) {
+// Shapes whose workspace holds the tile records and the work counter.
+static bool uses_records(int dtype, int H_r, int H_s, int d_h) {
   return dtype == HF_BF16 && d_h == kDH && (H_r == 4 || H_r == 8) && H_s <= kHMax;
 }
 
 size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h) {
-  return uses_tiled(dtype, H_r, H_s, d_h) ? kRecBytes : 0;
+  return uses_records(dtype, H_r, H_s, d_h) ? kRecBytes : 0;
 }
 
 int transfer_persistent_grid(const TransferArgs& a, int n_cu) {
@@ -1133,7 +989,7 @@ int transfer_persistent_grid(const TransferArgs& a, int n_cu) {
 
 hipError_t launch_transfer_stage(int dtype, const TransferArgs& a, hipStream_t s) {
   const int tiles = a.tile_start[a.B];
-  if (!uses_tiled(dtype, a.H_r, a.H_s, a.d_h) || tiles <= 0) return hipSuccess;
+  if (!uses_records(dtype, a.H_r, a.H_s, a.d_h) || tiles <= 0) return hipSuccess;
   if (!a.tile_rec) return hipErrorInvalidValue;
   if (!a.work_ctr || a.n_wg < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(stage_tiles_kernel, dim3((unsigned)tiles), dim3(512), 0, s, a,
@@ -1216,27 +1072,27 @@ hipError_t launch_transfer(int dtype, const TransferArgs& a, hipStream_t s) {
   const long long items = (long long)a.tiles_per_lc * a.L_r * 2;
   if (items <= 0) return hipSuccess;
   const dim3 grid((unsigned)items);
-  const bool tiled = uses_tiled(dtype, a.H_r, a.H_s, a.d_h);
-  if (tiled && (!a.tile_rec || !a.work_ctr || a.n_wg < 1)) return hipErrorInvalidValue;
+  const bool rec = uses_records(dtype, a.H_r, a.H_s, a.d_h);
+  if (rec && (!a.tile_rec || !a.work_ctr || a.n_wg < 1)) return hipErrorInvalidValue;
   const dim3 pgrid((unsigned)a.n_wg);  // persistent (interpolating map): one workgroup per CU
+  const dim3 block(512);
   if (dtype == HF_BF16) {
-    switch (a.H_r) {
-      case 2: hipLaunchKernelGGL(transfer_bf16_direct_kernel<2>, grid, dim3(512), 0, s, a); break;
-      case 4:
-        if (tiled && a.concat)
-          hipLaunchKernelGGL((transfer_bf16_tiled_kernel<2, true>), grid, dim3(512), 0, s, a);
-        else if (tiled)
-          hipLaunchKernelGGL((transfer_bf16_tiled_kernel<2, false>), pgrid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL(transfer_bf16_direct_kernel<4>, grid, dim3(512), 0, s, a);
-        break;
-      case 8:
-        if (tiled && a.concat)
-          hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, true>), grid, dim3(512), 0, s, a);
-        else if (tiled)
-          hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, false>), pgrid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL(transfer_bf16_direct_kernel<8>, grid, dim3(512), 0, s, a);
-        break;
-      default: return hipErrorInvalidValue;
+    const bool multi = a.concat || a.H_s > kHMax;  // several passes over the X tile
+    if (rec && a.H_r == 8) {
+      if (multi) hipLaunchKernelGGL((transfer_bf16_tiled_kernel<8, true, false>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((transfer_bf16_tiled_kernel<8, false, false>), pgrid, block, 0, s, a);
+    } else if (rec) {
+      if (multi) hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, true, false>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, false, false>), pgrid, block, 0, s, a);
+    } else if (a.H_r == 8) {
+      hipLaunchKernelGGL((transfer_bf16_tiled_kernel<8, true, true>), grid, block, 0, s, a);
+    } else if (a.H_r == 4) {
+      hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, true, true>), grid, block, 0, s, a);
+    } else if (a.H_r == 2) {
+      if (multi) hipLaunchKernelGGL((transfer_bf16_tiled_kernel<2, true, true>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((transfer_bf16_tiled_kernel<2, false, true>), grid, block, 0, s, a);
+    } else {
+      return hipErrorInvalidValue;
     }
   } else {
     return launch_transfer_f32(a, s);
