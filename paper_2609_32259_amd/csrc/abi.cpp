@@ -102,6 +102,12 @@ class TimedLaunch {
   bool active_ = false;
 };
 
+bool profiling() {
+  Profiler& p = prof();
+  std::lock_guard<std::mutex> g(p.mu);
+  return p.on;
+}
+
 // Collect finished event pairs into the totals (waits for them).
 int32_t drain_profiler(Profiler& p) {
   for (EventPair& e : p.pending) {
@@ -349,13 +355,15 @@ int32_t hf_pack_maps(int32_t L_r, int32_t d_r, int32_t d_in, int32_t dtype, cons
 namespace {
 
 struct RopeSizes {
-  int P_s = 0, P_r = 0;  // table rows (0 = table not needed)
+  int P_s = 0, P_r = 0;    // table rows (0 = table not needed)
+  int lo_s = 0, lo_r = 0;  // first row some token sits at
 };
 
 int32_t rope_sizes(int32_t B, const int32_t* s_len, const int32_t* r_len, const hf_rope* rope,
                    RopeSizes& rs) {
   rs = RopeSizes();
   if (!rope) return HF_OK;
+  int lo_s = INT32_MAX, lo_r = INT32_MAX;
   for (int b = 0; b < B; ++b) {
     const int64_t ps = rope->pos0_s ? rope->pos0_s[b] : 0;
     const int64_t pr = rope->pos0_r ? rope->pos0_r[b] : 0;
@@ -364,7 +372,11 @@ int32_t rope_sizes(int32_t B, const int32_t* s_len, const int32_t* r_len, const 
       return fail(HF_ERR_SHAPE, "RoPE positions overflow int32");
     if (rope->unrotate_sender_k) rs.P_s = std::max(rs.P_s, (int)(ps + s_len[b]));
     if (rope->rotate_receiver_k) rs.P_r = std::max(rs.P_r, (int)(pr + r_len[b]));
+    if (s_len[b] > 0) lo_s = std::min(lo_s, (int)ps);
+    if (r_len[b] > 0) lo_r = std::min(lo_r, (int)pr);
   }
+  rs.lo_s = std::min(lo_s, rs.P_s);
+  rs.lo_r = std::min(lo_r, rs.P_r);
   // The bf16 kernels also read the rotations of the small offsets 0..15.
   if (rs.P_s > 0) rs.P_s = std::max(rs.P_s, hf::kRopeDeltaRows);
   return HF_OK;
@@ -657,18 +669,26 @@ int32_t transfer_impl(int32_t B, const int32_t* s_len, const int32_t* r_len,
     a.n_wg = hf::transfer_persistent_grid(a, n_cu > 0 ? n_cu : 1);
   }
   hipError_t e = hipSuccess;
-  if (a.unrot || a.rot) {
-    TimedLaunch t(HF_KERNEL_ROPE_TABLES, s, timed);
-    if (a.unrot) e = hf::launch_rope_table(const_cast<float*>(a.cs_s), rs.P_s, d_h, rope->theta_s, s);
-    if (e == hipSuccess && a.rot)
-      e = hf::launch_rope_table(const_cast<float*>(a.cs_r), rs.P_r, d_h, rope->theta_r, s);
-    if (e == hipSuccess && a.rot && staged)  // positions 0..31 for the staged epilogue
-      e = hf::launch_rope_table(const_cast<float*>(a.cs_t1), 32, d_h, rope->theta_r, s);
+  hf::RopeTabs tabs;
+  std::memset(&tabs, 0, sizeof tabs);
+  // the bf16 kernels read the rotations of the offsets 0..15 besides the sequences' rows
+  if (a.unrot)
+    tabs.t[tabs.n++] = {const_cast<float*>(a.cs_s), rope->theta_s, hf::kRopeDeltaRows, rs.lo_s, rs.P_s, 0, 0};
+  if (a.rot) tabs.t[tabs.n++] = {const_cast<float*>(a.cs_r), rope->theta_r, 0, rs.lo_r, rs.P_r, 0, 0};
+  if (a.rot && staged)  // positions 0..31 for the staged epilogue
+    tabs.t[tabs.n++] = {const_cast<float*>(a.cs_t1), rope->theta_r, 0, 0, 32, 0, 0};
+  // One launch for the tables and the records; two while the profiler is on, which
+  // times them apart.
+  const bool apart = timed && tabs.n > 0 && a.tile_rec && profiling();
+  if (apart || !a.tile_rec) {
+    TimedLaunch t(HF_KERNEL_ROPE_TABLES, s, timed && tabs.n > 0);
+    e = hf::launch_prologue(dtype, a, false, tabs, s);
+    tabs.n = 0;
   }
   if (e != hipSuccess) return hip_fail(e, "RoPE table launch");
   if (a.tile_rec) {
     TimedLaunch t(HF_KERNEL_TRANSFER_STAGE, s, timed);
-    e = hf::launch_transfer_stage(dtype, a, s);
+    e = hf::launch_prologue(dtype, a, true, tabs, s);
   }
   if (e != hipSuccess) return hip_fail(e, "tile staging launch");
   if (staged) {

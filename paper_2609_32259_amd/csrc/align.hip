@@ -1,20 +1,23 @@
 // Cross-tokenizer alignment kernels (Sec. 3.1 "Token Alignment"; App. B.1),
 // producing the CSR span table described in heterofold.h.
 //
-// Integer-only, three launches:
-//   1. align_count: per receiver token, binary searches over the sender
-//      spans give the TA partner (sender token ending at the same character)
-//      and the number of overlapping sender tokens.  Per-workgroup totals go
-//      to the workspace.  The counts and partners are parked in row_ptr / den.
-//   2. align_scan: one workgroup scans the per-workgroup totals (entry
-//      offsets) and the per-workgroup last partners (forward fill carried
-//      across workgroups of the same sequence), and finds each sequence's
-//      first nonempty sender token.
-//   3. align_fill: per receiver token, the final offsets and forward-filled
-//      partner, then the entries themselves.
-// Each receiver row is handled by the same thread in launches 1 and 3, and
-// rows' parked values live in their own slots, so no launch reads another
-// workgroup's parked data.
+// Integer-only.  Per receiver token, binary searches over the sender spans give
+// the TA partner (sender token ending at the same character) and the number of
+// overlapping sender tokens; an exclusive scan of the counts gives the entry
+// offsets and a forward fill of the partners the fallback, after which each row
+// writes its entries.  What bounds it is latency: the searches' chains of
+// loads (the three of a row advance together), and the launches, about 6 us each
+// whatever they do.  So:
+//   * up to kOneBlockRows rows: one workgroup does everything (align_one_kernel);
+//   * otherwise align_count writes each workgroup's totals, the counts and
+//     partners are parked in row_ptr / den, and align_fill sums the totals of the
+//     workgroups before its own.  Each receiver row is handled by the same thread
+//     in both, and rows' parked values live in their own slots, so no launch
+//     reads another workgroup's parked data;
+//   * past kScanBlocks workgroups, where every workgroup summing all before it
+//     would be quadratic, one workgroup scans the totals in between (align_scan).
+// 178 rows: 9.8 us; 1,821 rows: 8.0 + 9.2 us; 7,300 rows: 9.6 + 10.4 us.  Three
+// launches, with one search after the other, took 20, 28 and 34 us.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 
@@ -24,30 +27,35 @@ namespace hf {
 namespace {
 
 constexpr int kScanThreads = 1024;
+constexpr int kOneBlockRows = 1024;
+constexpr int kScanBlocks = 1024;
 
-__device__ __forceinline__ int upper_bound_dev(const int32_t* a, int n, int x) {
-  int lo = 0, hi = n;  // first index with a[i] > x
-  while (lo < hi) {
-    int mid = (lo + hi) >> 1;
-    if (a[mid] > x) hi = mid; else lo = mid + 1;
+// One binary search over a[0..n).
+// A step is a load at a position that is inside whenever the array is not
+// empty, then the comparison, so that the loads of several searches go out
+// together.
+struct Search {
+  const int32_t* a;
+  int lo, hi, n;
+  __device__ __forceinline__ Search(const int32_t* a_, int n_, bool on)
+      : a(a_), lo(0), hi(on ? n_ : 0), n(n_) {}
+  __device__ __forceinline__ int probe() const { return a[min((lo + hi) >> 1, n - 1)]; }
+  __device__ __forceinline__ void advance(bool right_of_mid) {
+    const int mid = (lo + hi) >> 1;
+    const bool open = lo < hi;
+    hi = open && !right_of_mid ? mid : hi;
+    lo = open && right_of_mid ? mid + 1 : lo;
   }
-  return lo;
-}
-
-__device__ __forceinline__ int lower_bound_dev(const int32_t* a, int n, int x) {
-  int lo = 0, hi = n;  // first index with a[i] >= x
-  while (lo < hi) {
-    int mid = (lo + hi) >> 1;
-    if (a[mid] >= x) hi = mid; else lo = mid + 1;
-  }
-  return lo;
-}
+};
 
 struct Plus {
   __device__ long long operator()(long long a, long long b) const { return a + b; }
 };
 struct LastValid {  // keeps the right operand unless it is "none" (negative)
   __device__ long long operator()(long long a, long long b) const { return b >= 0 ? b : a; }
+};
+struct Max {
+  __device__ long long operator()(long long a, long long b) const { return b > a ? b : a; }
 };
 struct Min {
   __device__ long long operator()(long long a, long long b) const { return b < a ? b : a; }
@@ -102,16 +110,26 @@ __device__ __forceinline__ RowInfo row_info(const AlignArgs& p, const int32_t* s
                                             const int32_t* se, int Ts, int rb, int re) {
   RowInfo r;
   r.partner = -1;
+  r.count = 1;
+  r.lo = r.hi = 0;
+  const bool overlap = p.mode == HF_ALIGN_OVERLAP;
+  // the last sender token ending at or before re; in overlap mode the first one
+  // ending after rb and the first one starting at or after re
+  Search past(se, Ts, rb < re), first(se, Ts, overlap), end(sb, Ts, overlap);
+  for (int n = Ts; n > 0; n >>= 1) {
+    const int v0 = past.probe(), v1 = first.probe(), v2 = end.probe();
+    past.advance(!(v0 > re));
+    first.advance(!(v1 > rb));
+    end.advance(!(v2 >= re));
+  }
   if (rb < re) {
-    int i = upper_bound_dev(se, Ts, re) - 1;  // last sender token ending at or before re
+    int i = past.lo - 1;
     while (i >= 0 && se[i] == re && !(sb[i] < se[i])) --i;  // skip empty tokens at re
     if (i >= 0 && se[i] == re && sb[i] < se[i]) r.partner = i;
   }
-  r.count = 1;
-  r.lo = r.hi = 0;
-  if (p.mode == HF_ALIGN_OVERLAP) {
-    r.lo = upper_bound_dev(se, Ts, rb);  // first sender token ending after rb
-    r.hi = lower_bound_dev(sb, Ts, re);  // first sender token starting at or after re
+  if (overlap) {
+    r.lo = first.lo;
+    r.hi = end.lo;
     int c = 0;
     for (int i = r.lo; i < r.hi; ++i) {
       int o = min(se[i], re) - max(sb[i], rb);
@@ -120,6 +138,90 @@ __device__ __forceinline__ RowInfo row_info(const AlignArgs& p, const int32_t* s
     r.count = c;
   }
   return r;
+}
+
+// Row g's offset, entries and denominator: entries from `off`, the fallback (its
+// own TA partner, or the one filled forward) `a`.
+__device__ __forceinline__ void write_row(const AlignArgs& p, int g, long long off, int a,
+                                          const RowInfo& r, const int32_t* sb, const int32_t* se,
+                                          int rb, int re) {
+  p.row_ptr[g] = (int32_t)(off < p.cap ? off : p.cap);
+  if (p.mode == HF_ALIGN_TA || r.count == 0) {
+    if (off < p.cap) {
+      p.col[off] = a;
+      p.num[off] = 1;
+    }
+    p.den[g] = 1;
+    return;
+  }
+  int total = 0;
+  long long e = off;
+  for (int i = r.lo; i < r.hi; ++i) {
+    int o = min(se[i], re) - max(sb[i], rb);
+    if (o > 0) {
+      if (e < p.cap) {
+        p.col[e] = i;
+        p.num[e] = o;
+      }
+      ++e;
+      total += o;
+    }
+  }
+  p.den[g] = total;
+}
+
+// First nonempty token of sb / se [0, Ts), 0 if there is none, by a workgroup of
+// NT threads (all must call it).
+template <int NT>
+__device__ int first_nonempty(const int32_t* sb, const int32_t* se, int Ts, long long* smem) {
+  for (int base = 0; base < Ts; base += NT) {
+    const int i = base + (int)threadIdx.x;
+    long long cand = LLONG_MAX;
+    if (i < Ts && sb[i] < se[i]) cand = i;
+    long long m;
+    block_inclusive_scan<NT>(cand, Min(), LLONG_MAX, smem, m);
+    if (m != LLONG_MAX) return (int)m;
+  }
+  return 0;
+}
+
+// The whole alignment of up to kOneBlockRows receiver rows, one per thread.
+__global__ __launch_bounds__(kOneBlockRows) void align_one_kernel(const AlignArgs p) {
+  __shared__ long long red[kOneBlockRows / 64];
+  __shared__ int need[HF_MAX_BATCH];
+  __shared__ int first[HF_MAX_BATCH];
+  const int g = threadIdx.x;
+  const bool valid = g < p.total_rows;
+  int b = 0;
+  while (b + 1 < p.B && p.r0[b + 1] <= g) ++b;
+  const int32_t* sb = p.s_beg + p.s0[b];
+  const int32_t* se = p.s_end + p.s0[b];
+  if (g < HF_MAX_BATCH) need[g] = 0;
+  RowInfo r{-1, 0, 0, 0};
+  int rb = 0, re = 0;
+  long long cnt = 0, part = -1;
+  if (valid) {
+    rb = p.r_beg[g];
+    re = p.r_end[g];
+    r = row_info(p, sb, se, p.Ts[b], rb, re);
+    cnt = r.count > 0 ? r.count : 1;
+    // tagged with the sequence, so that a fill never crosses sequences
+    if (r.partner >= 0) part = ((long long)b << 32) | r.partner;
+  }
+  long long tot, tl;
+  const long long off = block_inclusive_scan<kOneBlockRows>(cnt, Plus(), 0, red, tot) - cnt;
+  const long long fill = block_inclusive_scan<kOneBlockRows>(part, LastValid(), -1, red, tl);
+  const bool none = valid && !(fill >= 0 && (int)(fill >> 32) == b);
+  if (none) need[b] = 1;
+  __syncthreads();
+  for (int q = 0; q < p.B; ++q) {
+    if (!need[q]) continue;
+    const int f = first_nonempty<kOneBlockRows>(p.s_beg + p.s0[q], p.s_end + p.s0[q], p.Ts[q], red);
+    if (g == 0) first[q] = f;
+  }
+  __syncthreads();
+  if (valid) write_row(p, g, off, none ? first[b] : (int)(fill & 0xffffffffLL), r, sb, se, rb, re);
+  if (g == 0) p.row_ptr[p.total_rows] = (int32_t)(tot < p.cap ? tot : p.cap);
 }
 
 __global__ __launch_bounds__(kAlignBlock) void align_count_kernel(const AlignArgs p) {
@@ -157,19 +259,8 @@ __global__ __launch_bounds__(kScanThreads) void align_scan_kernel(const AlignArg
 
   // First nonempty sender token of each sequence (0 if there is none).
   for (int b = 0; b < p.B; ++b) {
-    long long found = LLONG_MAX;
-    for (int base = 0; base < p.Ts[b]; base += kScanThreads) {
-      int i = base + tid;
-      long long cand = LLONG_MAX;
-      if (i < p.Ts[b] && p.s_beg[p.s0[b] + i] < p.s_end[p.s0[b] + i]) cand = i;
-      long long m;
-      block_inclusive_scan<kScanThreads>(cand, Min(), LLONG_MAX, red, m);
-      if (m != LLONG_MAX) {
-        found = m;
-        break;
-      }
-    }
-    if (tid == 0) first_ne[b] = (found == LLONG_MAX) ? 0 : (int)found;
+    const int f = first_nonempty<kScanThreads>(p.s_beg + p.s0[b], p.s_end + p.s0[b], p.Ts[b], red);
+    if (tid == 0) first_ne[b] = f;
   }
   __syncthreads();
 
@@ -199,6 +290,8 @@ __global__ __launch_bounds__(kScanThreads) void align_scan_kernel(const AlignArg
   if (tid == 0) p.row_ptr[p.total_rows] = (int32_t)(sum_carry < p.cap ? sum_carry : p.cap);
 }
 
+// SCANNED: align_scan has left each workgroup's offset and carried partner.
+template <bool SCANNED>
 __global__ __launch_bounds__(kAlignBlock) void align_fill_kernel(const AlignArgs p) {
   __shared__ long long red[kAlignBlock / 64];
   const int blk = blockIdx.x;
@@ -206,48 +299,36 @@ __global__ __launch_bounds__(kAlignBlock) void align_fill_kernel(const AlignArgs
   const int j = (blk - p.blk_start[b]) * kAlignBlock + threadIdx.x;
   const bool valid = j < p.Tr[b];
   const int g = p.r0[b] + j;
-  long long cnt = valid ? p.row_ptr[g] : 0;
-  long long part = valid ? p.den[g] : -1;
-  long long tot;
-  long long off = block_inclusive_scan<kAlignBlock>(cnt, Plus(), 0, red, tot) - cnt + p.blk_off[blk];
-  long long fill = block_inclusive_scan<kAlignBlock>(part, LastValid(), -1, red, tot);
-  if (!valid) return;
-  const int a = fill >= 0 ? (int)fill : p.blk_carry[blk];
-  p.row_ptr[g] = (int32_t)(off < p.cap ? off : p.cap);
-  if (p.mode == HF_ALIGN_TA) {
-    if (off < p.cap) {
-      p.col[off] = a;
-      p.num[off] = 1;
-    }
-    p.den[g] = 1;
-    return;
-  }
   const int32_t* sb = p.s_beg + p.s0[b];
   const int32_t* se = p.s_end + p.s0[b];
-  const int rb = p.r_beg[g], re = p.r_end[g];
-  RowInfo r = row_info(p, sb, se, p.Ts[b], rb, re);
-  if (r.count == 0) {
-    if (off < p.cap) {
-      p.col[off] = a;
-      p.num[off] = 1;
+  long long cnt = valid ? p.row_ptr[g] : 0;
+  long long part = valid ? p.den[g] : -1;
+  const int rb = valid ? p.r_beg[g] : 0, re = valid ? p.r_end[g] : 0;
+  RowInfo r{-1, 1, 0, 0};
+  if (valid && p.mode == HF_ALIGN_OVERLAP) r = row_info(p, sb, se, p.Ts[b], rb, re);
+  long long tot;
+  long long base, carry;
+  if (SCANNED) {
+    base = p.blk_off[blk];
+    carry = p.blk_carry[blk];
+  } else {  // the totals of the workgroups before this one
+    long long sum = 0, last = -1;
+    for (int k = threadIdx.x; k < blk; k += kAlignBlock) {
+      sum += p.blk_sum[k];
+      if (k >= p.blk_start[b] && p.blk_last[k] >= 0) last = ((long long)k << 32) | p.blk_last[k];
     }
-    p.den[g] = 1;
-    return;
+    block_inclusive_scan<kAlignBlock>(sum, Plus(), 0, red, base);
+    block_inclusive_scan<kAlignBlock>(last, Max(), -1, red, tot);
+    carry = tot >= 0 ? (tot & 0xffffffffLL) : -1;
   }
-  int total = 0;
-  long long e = off;
-  for (int i = r.lo; i < r.hi; ++i) {
-    int o = min(se[i], re) - max(sb[i], rb);
-    if (o > 0) {
-      if (e < p.cap) {
-        p.col[e] = i;
-        p.num[e] = o;
-      }
-      ++e;
-      total += o;
-    }
-  }
-  p.den[g] = total;
+  const long long off = block_inclusive_scan<kAlignBlock>(cnt, Plus(), 0, red, tot) - cnt + base;
+  if (!SCANNED && blk == p.nblk - 1 && threadIdx.x == 0)
+    p.row_ptr[p.total_rows] = (int32_t)(base + tot < p.cap ? base + tot : p.cap);
+  const long long fill = block_inclusive_scan<kAlignBlock>(part, LastValid(), -1, red, tot);
+  if (!SCANNED && carry < 0 && __syncthreads_or(valid && fill < 0))
+    carry = first_nonempty<kAlignBlock>(sb, se, p.Ts[b], red);
+  if (!valid) return;
+  write_row(p, g, off, fill >= 0 ? (int)fill : (int)carry, r, sb, se, rb, re);
 }
 
 }  // namespace
@@ -259,13 +340,18 @@ size_t align_workspace_bytes(int nblk) {
 }
 
 hipError_t launch_alignment(const AlignArgs& a, hipStream_t s) {
-  if (a.nblk > 0) {
-    hipLaunchKernelGGL(align_count_kernel, dim3(a.nblk), dim3(kAlignBlock), 0, s, a);
+  const dim3 grid((unsigned)a.nblk), block(kAlignBlock);
+  if (a.total_rows > 0 && a.total_rows <= kOneBlockRows) {
+    hipLaunchKernelGGL(align_one_kernel, dim3(1), dim3(kOneBlockRows), 0, s, a);
+    return hipGetLastError();
+  }
+  if (a.nblk > 0) hipLaunchKernelGGL(align_count_kernel, grid, block, 0, s, a);
+  if (a.nblk > 0 && a.nblk <= kScanBlocks) {
+    hipLaunchKernelGGL(align_fill_kernel<false>, grid, block, 0, s, a);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(align_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, a);
-  if (a.nblk > 0) {
-    hipLaunchKernelGGL(align_fill_kernel, dim3(a.nblk), dim3(kAlignBlock), 0, s, a);
-  }
+  if (a.nblk > 0) hipLaunchKernelGGL(align_fill_kernel<true>, grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -106,15 +106,27 @@ hipError_t launch_staged_gemm(const TransferArgs& a, hipStream_t s);
 int transfer_rows_per_tile(int dtype, int H_r, int H_s, int n_taps, int d_h);
 int transfer_f32_rows_per_tile(int H_s, int n_taps, int d_h);
 // Device bytes of the staging record each row tile needs (0 where the kernel
-// that runs keeps no records), and the launch that writes the records
-// (a.tile_rec, one per tile of the batch) before launch_transfer.
+// that runs keeps no records).
 size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h);
 // Workgroups of the persistent tiled kernel on a device with n_cu compute units.
 int transfer_persistent_grid(const TransferArgs& a, int n_cu);
-hipError_t launch_transfer_stage(int dtype, const TransferArgs& a, hipStream_t s);
+// A RoPE table to fill: rows [0, head) and [lo, P) of tab (head 0: [lo, P) only).
+struct RopeTab {
+  float* tab;
+  double theta;
+  int head, lo, P;
+  int ppt, blocks;  // set by the launch
+};
+struct RopeTabs {
+  int n;
+  RopeTab t[3];
+};
+// The staging records (where `stage` and the kernel that runs keeps them) and the
+// RoPE tables of a transfer, in one launch (none if there is nothing to do).
+hipError_t launch_prologue(int dtype, const TransferArgs& a, bool stage, const RopeTabs& tabs,
+                           hipStream_t s);
 
 hipError_t launch_alignment(const AlignArgs& a, hipStream_t s);
-hipError_t launch_rope_table(float* tab, int P, int d_h, double theta, hipStream_t s);
 // Writes the header and the packed maps (A_packed: hf_packed_maps_bytes bytes).
 hipError_t launch_pack_maps(int dtype, int n_lc, int d_r, int d_in, const void* A, void* A_packed,
                             hipStream_t s);

@@ -45,23 +45,24 @@ __device__ __forceinline__ void copy16_to_lds(const void* gsrc, void* lds_wave_b
 
 // ---------------------------------------------------------------------------
 // RoPE tables: row pos holds cos(pos w_k) for k < d/2, then sin(pos w_k), with
-// w_k = theta^(-2k/d); the angle is formed in fp64.
+// w_k = theta^(-2k/d); the angle is formed in fp64.  Only the rows a call reads
+// are written: [0, head) and [lo, P).
+// A workgroup of 512 threads owns 64 angles (k) and 8 ppt rows; each thread forms
+// its w_k once, for ppt rows.
 // ---------------------------------------------------------------------------
-// A thread owns one angle index k (threadIdx.x + 64 blockIdx.y) and kRopePpt
-// consecutive positions, so w_k is formed once per thread.
-constexpr int kRopePpt = 16;
-__global__ __launch_bounds__(256) void rope_table_kernel(float* tab, int P, int half, int d,
-                                                         double theta) {
-  const int k = blockIdx.y * 64 + threadIdx.x;
+__device__ __forceinline__ void rope_rows(const RopeTab& t, int blk, int half, int d) {
+  const int n_k = (half + 63) / 64;
+  const int k = (blk % n_k) * 64 + (threadIdx.x & 63);
   if (k >= half) return;
-  const double w = pow(theta, -2.0 * k / d);
-  const long long p0 = ((long long)blockIdx.x * 4 + threadIdx.y) * kRopePpt;
-  const int p1 = (int)min(p0 + kRopePpt, (long long)P);
-  for (int pos = (int)min(p0, (long long)P); pos < p1; ++pos) {
+  const double w = pow(t.theta, -2.0 * k / d);
+  const int rows = t.head + (t.P - t.lo);
+  const int v0 = ((blk / n_k) * 8 + (int)(threadIdx.x >> 6)) * t.ppt;
+  for (int v = v0; v < min(v0 + t.ppt, rows); ++v) {
+    const int pos = v < t.head ? v : t.lo + (v - t.head);
     double s, c;
     sincos((double)pos * w, &s, &c);
-    tab[(long long)pos * d + k] = (float)c;
-    tab[(long long)pos * d + half + k] = (float)s;
+    t.tab[(long long)pos * d + k] = (float)c;
+    t.tab[(long long)pos * d + half + k] = (float)s;
   }
 }
 
@@ -528,12 +529,29 @@ __device__ __forceinline__ void stage_tile(const TransferArgs& p, int t, int* en
   __syncthreads();
 }
 
-__global__ __launch_bounds__(512) void stage_tiles_kernel(const TransferArgs p, int* rec) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p.work_ctr = p.n_wg;  // items [0, n_wg) start statically
+// What a transfer needs before its kernels, in one launch (each costs 5 to 6 us on
+// the GPU whatever it does: a call on 200 tokens took 18 us for two tables and the
+// records, 5.7 now): first the staging of the tiles (n_stage workgroups),
+// then the RoPE tables.
+__global__ __launch_bounds__(512) void prologue_kernel(const TransferArgs p, int* rec, int n_stage,
+                                                       const RopeTabs r) {
   __shared__ __attribute__((aligned(16))) int ent[kRecBytes / 4];
-  stage_tile(p, blockIdx.x, ent);
-  int4* dst = reinterpret_cast<int4*>(rec + (long long)blockIdx.x * (kRecBytes / 4));
-  dst[threadIdx.x] = reinterpret_cast<const int4*>(ent)[threadIdx.x];
+  int blk = blockIdx.x;
+  if (blk < n_stage) {
+    if (blk == 0 && threadIdx.x == 0) *p.work_ctr = p.n_wg;  // items [0, n_wg) start statically
+    stage_tile(p, blk, ent);
+    int4* dst = reinterpret_cast<int4*>(rec + (long long)blk * (kRecBytes / 4));
+    dst[threadIdx.x] = reinterpret_cast<const int4*>(ent)[threadIdx.x];
+    return;
+  }
+  blk -= n_stage;
+  for (int i = 0; i < r.n; ++i) {
+    if (blk < r.t[i].blocks) {
+      rope_rows(r.t[i], blk, p.d_h / 2, p.d_h);
+      return;
+    }
+    blk -= r.t[i].blocks;
+  }
 }
 
 // HR: receiver heads.  MULTI: several passes over the X tile (concatenated taps,
@@ -987,22 +1005,29 @@ int transfer_persistent_grid(const TransferArgs& a, int n_cu) {
   return (int)(items < n_cu ? items : n_cu);
 }
 
-hipError_t launch_transfer_stage(int dtype, const TransferArgs& a, hipStream_t s) {
-  const int tiles = a.tile_start[a.B];
-  if (!uses_records(dtype, a.H_r, a.H_s, a.d_h) || tiles <= 0) return hipSuccess;
-  if (!a.tile_rec) return hipErrorInvalidValue;
-  if (!a.work_ctr || a.n_wg < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(stage_tiles_kernel, dim3((unsigned)tiles), dim3(512), 0, s, a,
-                     const_cast<int*>(a.tile_rec));
-  return hipGetLastError();
-}
-
-hipError_t launch_rope_table(float* tab, int P, int d_h, double theta, hipStream_t s) {
-  const int half = d_h / 2;
-  const long long n = (long long)P * half;
-  if (n <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((P + 4 * kRopePpt - 1) / (4 * kRopePpt)), (unsigned)((half + 63) / 64));
-  hipLaunchKernelGGL(rope_table_kernel, grid, dim3(64, 4), 0, s, tab, P, half, d_h, theta);
+hipError_t launch_prologue(int dtype, const TransferArgs& a, bool stage, const RopeTabs& tabs,
+                           hipStream_t s) {
+  int n_stage = 0;
+  if (stage && uses_records(dtype, a.H_r, a.H_s, a.d_h)) {
+    n_stage = a.tile_start[a.B];
+    if (n_stage > 0 && (!a.tile_rec || !a.work_ctr || a.n_wg < 1)) return hipErrorInvalidValue;
+  }
+  RopeTabs r = tabs;
+  const int half = a.d_h / 2, n_k = (half + 63) / 64;
+  long long blocks = n_stage;
+  for (int i = 0; i < r.n; ++i) {
+    RopeTab& t = r.t[i];
+    t.head = t.head < t.lo ? t.head : 0;  // rows [0, head) below the range
+    if (t.head == 0 && tabs.t[i].head > 0) t.lo = 0;
+    const int rows = t.head + (t.P - t.lo);
+    // 16 rows share a w_k, fewer where that would leave the chip idle
+    t.ppt = rows >= 16384 ? 16 : rows >= 4096 ? 4 : 1;
+    t.blocks = n_k * ((rows + 8 * t.ppt - 1) / (8 * t.ppt));
+    blocks += t.blocks;
+  }
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(prologue_kernel, dim3((unsigned)blocks), dim3(512), 0, s, a,
+                     const_cast<int*>(a.tile_rec), n_stage, r);
   return hipGetLastError();
 }
 
