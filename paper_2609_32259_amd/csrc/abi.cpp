@@ -661,6 +661,7 @@ int32_t transfer_impl(int32_t B, const int32_t* s_len, const int32_t* r_len,
     a.xs_slab = (long long)rt * hf::kStagedRows * 1024;
   }
   if (tiles == 0) return ok();
+  hf::transfer_order(a);
   if (a.tile_rec) {
     int dev = 0, n_cu = 0;
     hipError_t de = hipGetDevice(&dev);

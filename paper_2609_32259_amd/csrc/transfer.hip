@@ -529,6 +529,41 @@ __device__ __forceinline__ void stage_tile(const TransferArgs& p, int t, int* en
   __syncthreads();
 }
 
+// Work items in p.n_queues queues; workgroup i takes queue i % n_queues.  One queue
+// is the plain order.  With eight, queue q holds the tiles of every eighth (layer,
+// role) from q on: workgroup i runs on XCD i % 8, so the workgroups of an XCD share
+// one map in its L2 (transfer_queues says when).
+constexpr int kMaxQueues = 8;
+constexpr int kCtrStride = 8;  // ints between the queues' counters (256 bytes in all)
+constexpr int kCtrTotal = 4;   // the count of all items taken, between the first two
+
+__device__ __forceinline__ int queue_items(const TransferArgs& p, int q) {
+  return p.tiles_per_lc * ((2 * p.L_r - q + p.n_queues - 1) / p.n_queues);
+}
+// Item v of queue q, in plain order.
+__device__ __forceinline__ int queue_item(const TransferArgs& p, int q, int v) {
+  const int i = v / p.tiles_per_lc;
+  return (p.n_queues * i + q) * p.tiles_per_lc + (v - i * p.tiles_per_lc);
+}
+// An item of the queues after `own` (which is empty), or n_items if they are too.
+__device__ __forceinline__ int other_queue_item(const TransferArgs& p, int own, int n_items) {
+  for (int i = 1; i < p.n_queues; ++i) {
+    const int q = (own + i) % p.n_queues, n = queue_items(p, q);
+    if (n <= 0) continue;
+    const int v = atomicAdd(p.work_ctr + q * kCtrStride, 1);
+    if (v < n) return queue_item(p, q, v);
+  }
+  return n_items;
+}
+// The next item for a workgroup of queue `own`, n_items if none is left.  A count of
+// all items taken goes along, so that the end is found with one look and not eight.
+__device__ __forceinline__ int next_item_of(const TransferArgs& p, int own, int n_items) {
+  const int v = atomicAdd(p.work_ctr + own * kCtrStride, 1);
+  const int t = atomicAdd(p.work_ctr + kCtrTotal, 1);
+  if (v < queue_items(p, own)) return queue_item(p, own, v);
+  return t < n_items ? other_queue_item(p, own, n_items) : n_items;
+}
+
 // What a transfer needs before its kernels, in one launch (each costs 5 to 6 us on
 // the GPU whatever it does: a call on 200 tokens took 18 us for two tables and the
 // records, 5.7 now): first the staging of the tiles (n_stage workgroups),
@@ -538,7 +573,11 @@ __global__ __launch_bounds__(512) void prologue_kernel(const TransferArgs p, int
   __shared__ __attribute__((aligned(16))) int ent[kRecBytes / 4];
   int blk = blockIdx.x;
   if (blk < n_stage) {
-    if (blk == 0 && threadIdx.x == 0) *p.work_ctr = p.n_wg;  // items [0, n_wg) start statically
+    if (blk == 0 && (int)threadIdx.x < p.n_queues) {  // a queue's first items start statically
+      const int q = threadIdx.x, wgs = (p.n_wg - q + p.n_queues - 1) / p.n_queues;
+      p.work_ctr[q * kCtrStride] = min(wgs, queue_items(p, q));
+      if (q == 0) p.work_ctr[kCtrTotal] = p.n_wg;
+    }
     stage_tile(p, blk, ent);
     int4* dst = reinterpret_cast<int4*>(rec + (long long)blk * (kRecBytes / 4));
     dst[threadIdx.x] = reinterpret_cast<const int4*>(ent)[threadIdx.x];
@@ -586,14 +625,23 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
     copy16_to_lds(rec + wave * 256 + 4 * lane, estart + wave * 256);
   };
 
-  // Persistent (interpolating map): the workgroup starts on work item
-  // blockIdx.x and takes the next one from the work counter (set to the grid
-  // size by the staging kernel) while it builds, so the items in flight stay a
-  // contiguous run of the work order, and the next record is copied in during
-  // the store.  With concatenated taps (whose per-tap passes leave no registers
-  // for the loop) a workgroup does the one item blockIdx.x.
+  // Persistent (interpolating map): the workgroup starts on item blockIdx.x / n_queues
+  // of its queue and takes the next one from the queue's counter (set to the
+  // queue's workgroups by the prologue) while it builds, so the items in flight stay
+  // a contiguous run of each queue, and the next record is copied in during the
+  // store.  With several passes (which leave no registers for the loop) a
+  // workgroup does one item.
   constexpr bool kPersist = !MULTI && !OWN;
-  int item = blockIdx.x;
+  const int queue = blockIdx.x % p.n_queues, first = blockIdx.x / p.n_queues;
+  int item;
+  if (!kPersist || first < queue_items(p, queue)) {
+    item = queue_item(p, queue, first);  // without the loop, the queues are equally long
+  } else {  // more workgroups than items in this queue
+    if (tid == 0) *next_item = other_queue_item(p, queue, n_items);
+    __syncthreads();
+    item = *next_item;
+    if (item >= n_items) return;
+  }
   if (OWN) stage_tile(p, item % p.tiles_per_lc, estart);
   else copy_record(item);
   if (p.unrot) {  // U(0..15): rows 0..15 of the sender table, 2 per wave
@@ -615,7 +663,7 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   const int e_base = estart[0];
   const bool staged = p.s_extent > 0 && flag[1] == 0 && !(unrot && flag[0] != 0);
   int grabbed = n_items;
-  if (kPersist && tid == 0) grabbed = atomicAdd(p.work_ctr, 1);
+  if (kPersist && tid == 0) grabbed = next_item_of(p, queue, n_items);
 
   f32x16 acc[MT][NTW];  // zeroed after the first pass's build
   // This wave's accumulators: receiver head `head`, n-tiles feat[q].
@@ -641,7 +689,9 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
     const int tap = pass / n_grp, h_first = OWN ? kHMax * (pass - tap * n_grp) : 0;
     const int Hp = OWN ? min(kHMax, H - h_first) : H;  // sender heads of this pass
     const int KS = Hp * (kDH / 16);                    // and its k-steps
-    const int ks0 = (int)((unsigned)item % (unsigned)Hp) * (kDH / 16);  // the first one
+    // The first one.  In plain order, where all workgroups share a map, they start at
+    // different sender heads; an XCD's few start at the same one and meet in its L2.
+    const int ks0 = (int)((unsigned)(p.n_queues > 1 ? lc_store : item) % (unsigned)Hp) * (kDH / 16);
     const Ctx ct = make_ctx(p, it, tap);
     // ---- build X[64][Hp d_h] of this pass ----
     if (staged) {
@@ -998,6 +1048,22 @@ static bool uses_records(int dtype, int H_r, int H_s, int d_h) {
 
 size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h) {
   return uses_records(dtype, H_r, H_s, d_h) ? kRecBytes : 0;
+}
+
+// Eight queues up to kQueueTiles row tiles, one past that.  In plain order the tiles
+// of a (layer, role) lie on all XCDs and each fetches the 2 MB map: of a 200-token
+// message's 92 us, 64 were that stream.  Kernel us in plain order, in eight queues,
+// and in eight queues with one start of the k-loop per map (32 -> 40 layers, 8 -> 8
+// heads): 200 tokens 93/86/61, 500 195/165/140, 1K 318/252/244, 2K 542/439/443, 4K
+// 897/852/843, 8K 1649/1638/1626; at 16K (229 tiles) 3166/3207/3175, at 32K one
+// queue is 1% faster.  8 -> 4 heads, 4K: 393/369/375.
+// A kernel of one item per workgroup needs queues of one length.
+constexpr int kQueueTiles = 128;
+
+void transfer_order(TransferArgs& a) {
+  const bool one_each = a.concat || a.H_s > kHMax || !uses_records(HF_BF16, a.H_r, a.H_s, a.d_h);
+  const bool even = 2 * a.L_r % kMaxQueues == 0;
+  a.n_queues = a.tiles_per_lc <= kQueueTiles && (even || !one_each) ? kMaxQueues : 1;
 }
 
 int transfer_persistent_grid(const TransferArgs& a, int n_cu) {
