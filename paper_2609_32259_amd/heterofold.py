@@ -66,7 +66,7 @@ class hf_recolor_info(C.Structure):
                 ("residual", C.c_double * 3)]
 
 
-_I32P = C.POINTER(C.c_int32)
+_I32P = C.c_void_p  # host int32 arrays, passed by address (_p32)
 _SIGNATURES = {
     "hf_last_error": (C.c_char_p, []),
     "hf_version": (C.c_int32, []),
@@ -163,13 +163,21 @@ def _i32(a) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
-def _p32(a: np.ndarray):
-    return a.ctypes.data_as(_I32P)
+def _p32(a: np.ndarray) -> int:
+    """Address of a host int32 array, which the caller keeps alive over the call
+    (0.2 us; a typed pointer from numpy's ctypes interface takes 1.6)."""
+    return a.__array_interface__["data"][0]
+
+
+_torch_module = None
 
 
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream(stream):
@@ -245,16 +253,16 @@ def hf_build_alignment(s_cu, r_cu, s_beg, s_end, r_beg, r_end, mode="overlap",
     s_cu, r_cu = _i32(s_cu), _i32(r_cu)
     B = s_cu.size - 1
     dev = s_beg.device
-    cap = hf_alignment_nnz_capacity(np.diff(s_cu), np.diff(r_cu), mode)
-    nR = int(r_cu[-1])
     if out is None:
+        cap = hf_alignment_nnz_capacity(np.diff(s_cu), np.diff(r_cu), mode)
+        nR = int(r_cu[-1])
         out = Alignment(torch.empty(nR + 1, dtype=torch.int32, device=dev),
                         torch.empty(max(cap, 1), dtype=torch.int32, device=dev),
                         torch.empty(max(cap, 1), dtype=torch.int32, device=dev),
                         torch.empty(max(nR, 1), dtype=torch.int32, device=dev), s_cu, r_cu)
-    wsb = hf_alignment_workspace_bytes(r_cu)
     if workspace is None:
-        workspace = torch.empty(max(wsb, 16), dtype=torch.uint8, device=dev)
+        workspace = torch.empty(max(hf_alignment_workspace_bytes(r_cu), 16), dtype=torch.uint8,
+                                device=dev)
     st = lib().hf_build_alignment(
         B, _p32(s_cu), _p32(r_cu), _dev_i32(s_beg, "s_beg"), _dev_i32(s_end, "s_end"),
         _dev_i32(r_beg, "r_beg"), _dev_i32(r_end, "r_end"), _mode_code(mode),
@@ -344,8 +352,9 @@ def make_rope(theta_s, theta_r, unrotate_sender_k=True, rotate_receiver_k=True,
     ps = None if pos0_s is None else _i32(pos0_s)
     pr = None if pos0_r is None else _i32(pos0_r)
     r = hf_rope(float(theta_s), float(theta_r), int(bool(unrotate_sender_k)),
-                int(bool(rotate_receiver_k)), _p32(ps) if ps is not None else None,
-                _p32(pr) if pr is not None else None)
+                int(bool(rotate_receiver_k)),
+                ps.ctypes.data_as(C.POINTER(C.c_int32)) if ps is not None else None,
+                pr.ctypes.data_as(C.POINTER(C.c_int32)) if pr is not None else None)
     return r, (ps, pr)
 
 
@@ -405,9 +414,10 @@ def hf_transfer_kv(s_len, r_len, alignment: Alignment, layer_map, S, R, A_packed
     sd, rd = kv_desc(S), kv_desc(R)
     rs, keep = _rope_struct(rope)
     os_ = _opts_struct(opts)
-    wsb = hf_transfer_workspace_bytes(s_len, r_len, S, R, rope)
-    if workspace is None and wsb > 0:
-        workspace = torch.empty(wsb, dtype=torch.uint8, device=S.device)
+    if workspace is None:
+        wsb = hf_transfer_workspace_bytes(s_len, r_len, S, R, rope)
+        if wsb > 0:
+            workspace = torch.empty(wsb, dtype=torch.uint8, device=S.device)
     if bias is not None and (bias.dtype != torch.float32 or not bias.is_contiguous()):
         raise TypeError("bias must be a contiguous fp32 tensor [L_r, 2, d_r]")
     st = lib().hf_transfer_kv(
@@ -463,9 +473,10 @@ def hf_transfer_kv_taps(s_len, r_len, alignment: Alignment, taps, S, R, A_packed
     sd, rd = kv_desc(S), kv_desc(R)
     rs, keep = _rope_struct(rope)
     os_ = _opts_struct(opts)
-    wsb = hf_transfer_workspace_bytes(s_len, r_len, S, R, rope)
-    if workspace is None and wsb > 0:
-        workspace = torch.empty(wsb, dtype=torch.uint8, device=S.device)
+    if workspace is None:
+        wsb = hf_transfer_workspace_bytes(s_len, r_len, S, R, rope)
+        if wsb > 0:
+            workspace = torch.empty(wsb, dtype=torch.uint8, device=S.device)
     if bias is not None and (bias.dtype != torch.float32 or not bias.is_contiguous()):
         raise TypeError("bias must be a contiguous fp32 tensor [L_r, 2, d_r]")
     st = lib().hf_transfer_kv_taps(
