@@ -72,9 +72,10 @@ def kernel_name(cfg):
     """The transfer kernel hf_transfer_kv(_taps) launches for this shape."""
     if cfg.dtype != "bf16":
         return "transfer_f32_kernel"
-    if cfg.H_r in (4, 8) and cfg.H_s <= 8:
-        return f"transfer_bf16_tiled_kernel<{cfg.H_r // 2}, {'true' if cfg.n_taps > 1 else 'false'}>"
-    return f"transfer_bf16_direct_kernel<{cfg.H_r}>"
+    records = cfg.H_r in (4, 8) and cfg.H_s <= 8
+    tf = lambda b: "true" if b else "false"  # noqa: E731
+    return (f"transfer_bf16_tiled_kernel<{cfg.H_r}, {tf(cfg.n_taps > 1 or cfg.H_s > 8)}, "
+            f"{tf(not records)}>")
 
 
 def kernel_traffic(cfg, staged=False):

@@ -459,7 +459,8 @@ typedef struct {
  * U Q^T when that matrix has full rank).  The steps are scaled, so that small
  * singular values grow by 9/4 a step instead of 3/2.  Each iteration stops three
  * steps after its residual falls below 1e-3, or after 48 (roots) / 88 (polar)
- * steps, which take singular values as small as 64 / 128 plain steps would; the call returns before the device finishes, so read info after the
+ * steps, which reach singular values as small as 64 / 128 plain steps would;
+ * the call returns before the device finishes, so read info after the
  * stream completes: converged[i] == 0 means the result is not valid (a
  * singular covariance without ridge, or a rank-deficient cross-covariance).
  */

@@ -255,7 +255,7 @@ def test_bf16_runs_too_wide_for_the_rotation_table(torch, H_r):
 
 
 def test_bf16_two_receiver_heads(torch):
-    cfg = synth.LLAMA8B_14B_8K.with_(name="8->2 heads", H_r=2, L_r=3, T_s=700)   # 256-row tiles
+    cfg = synth.LLAMA8B_14B_8K.with_(name="8->2 heads", H_r=2, L_r=3, T_s=700)
     wl = synth.make_workload(cfg, seed=5, device="cuda")
     _compare_full(torch, cfg, wl, "overlap")
 
@@ -391,8 +391,8 @@ def test_bf16_rows_past_length_untouched_and_deterministic(torch, staged):
 @pytest.mark.parametrize("H_s,H_r", [(1, 8), (2, 8), (2, 4), (16, 8), (16, 4)])
 def test_bf16_sender_head_counts(torch, H_s, H_r):
     # 1 and 2 sender heads: the tiled kernel with 8 and 4 waves per sender head;
-    # 16 sender heads: more than the tiled kernel's LDS tile holds, so the
-    # direct kernel runs.  Several row tiles with a ragged tail, RoPE on keys.
+    # 16 sender heads: more than the tiled kernel's LDS tile holds, so it takes
+    # two passes.  Several row tiles with a ragged tail, RoPE on keys.
     cfg = synth.LLAMA8B_14B_8K.with_(name=f"{H_s}->{H_r} heads", H_s=H_s, H_r=H_r, L_s=5,
                                      L_r=4, T_s=333)
     wl = synth.make_workload(cfg, seed=40 + H_s, device="cuda")
