@@ -458,10 +458,12 @@ typedef struct {
  * the whitened cross-covariance by the Newton-Schulz polar iteration (equal to
  * U Q^T when that matrix has full rank).  The steps are scaled, so that small
  * singular values grow by 9/4 a step instead of 3/2.  Each iteration stops three
- * steps after its residual falls below 1e-3, or after 48 (roots) / 88 (polar)
- * steps, which reach singular values as small as 64 / 128 plain steps would;
- * the call returns before the device finishes, so read info after the
- * stream completes: converged[i] == 0 means the result is not valid (a
+ * steps after its residual falls below 1e-3, or after 60 (roots) / 88 (polar)
+ * steps, which reach singular values as small as 64 / 128 plain steps would.
+ * The error of S^{1/2} grows as sqrt(kappa) eps and that of S^{-1/2} as kappa eps
+ * with the condition number kappa of S; past about 1e14 rounding keeps the roots
+ * from converging.  The call returns before the device finishes, so read info
+ * after the stream completes: converged[i] == 0 means the result is not valid (a
  * singular covariance without ridge, or a rank-deficient cross-covariance).
  */
 size_t hf_recolor_solve_workspace_bytes(int32_t p, int32_t q);

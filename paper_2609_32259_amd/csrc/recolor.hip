@@ -33,12 +33,16 @@ constexpr int kRedThreads = 256;
 constexpr int kMaxRedBlocks = 1024;
 
 // Newton-Schulz convergence: once the residual |I - P|_F falls below this, the
-// error contracts as e' = 3/4 e^2 + e^3/4, so three more steps reach rounding.
+// error contracts as e' = 3/4 e^2 + e^3/4, so three more steps reach rounding --
+// which for P = Z Y of the roots grows with the condition number of S (last residual
+// at 150 x 150: 5e-14 at 1e4, 3e-12 at 1e8, 2e-10 at 1e12).
 constexpr double kNsSwitch = 1e-3;
 constexpr int kNsExtra = 2;
 // Scaling of the steps (ns_update): the smallest singular value assumed at the
 // start, for the roots and for the polar factor, and the largest squared scale.
-constexpr double kNsFloorRoot = 3e-3;
+// Roots: 3e-2 takes 10, 14, 25 and 36 steps at condition numbers 10, 1e4, 1e8 and
+// 1e12 (3e-3: 13, 13, 22, 34; plain: 11, 19, 30, 41).
+constexpr double kNsFloorRoot = 3e-2;
 constexpr double kNsFloorPolar = 1e-2;
 constexpr double kNsMaxScale2 = 2.25;
 constexpr int kNsRestart = 20;
@@ -50,6 +54,7 @@ struct NsState {
   int arrived;    // workgroups that have left their share of the residual
   double res;     // last residual |I - P|_F
   double low;     // assumed lower bound of the iterate's singular values
+  double again;   // the bound when the scaling starts over (1: it does not)
   double alpha;   // this step is X' = beta X + alpha X P
   double beta;
 };
@@ -99,9 +104,13 @@ __device__ inline bool last_arrival(int* arrived, long long n) {
 // (Chen and Chow's scaling of the Newton-Schulz sign iteration); values
 // below l also grow and stay positive, so a bound assumed too high costs steps
 // and nothing else: where values are still small after kNsRestart steps, the
-// scaling starts over.  mu^2 <= 2.25 keeps the factor (3 - mu^2) / 2 that the
-// largest values meet at 3/8 or more, away from cancellation, for one more
-// step in a dozen.  mu = 1 exactly once the residual shows convergence.
+// scaling of the polar iteration starts over.  That of the roots does not: values
+// that have converged shrink by 3/8 in a scaled step and grow back, and the coupled
+// iterates do not correct the rounding of that (in fp64 on the host the error of
+// S^{1/2} is 2 to 3 times larger at condition numbers of 1e10 and more).
+// mu^2 <= 2.25 keeps the factor (3 - mu^2) / 2 that the largest values meet at 3/8
+// or more, away from cancellation, for one more step in a dozen.  mu = 1 exactly
+// once the residual shows convergence.
 __device__ inline void ns_update(NsState* st, double res) {
   st->res = res;
   if (st->extra == 0) {
@@ -115,7 +124,7 @@ __device__ inline void ns_update(NsState* st, double res) {
   st->iters += 1;
   double l = st->low;
   if (res < 0.3) l = 1.0;
-  else if (l > 0.9) l = st->iters >= kNsRestart ? kNsFloorPolar : 1.0;
+  else if (l > 0.9) l = st->iters >= kNsRestart ? st->again : 1.0;
   const double mu2 = fmin(kNsMaxScale2, 3.0 / (1.0 + l + l * l)), mu = sqrt(mu2);
   st->alpha = -0.5 * mu * mu2;
   st->beta = 1.5 * mu;
@@ -126,9 +135,8 @@ __device__ inline void ns_update(NsState* st, double res) {
 enum JobKind {
   kPlain = 0,
   kStep,     // D = st->alpha op(A) op(B) + st->beta C
-  kStepSym,  // the same with a symmetric result: upper tiles, mirrored
   kGram,     // P = op(A) op(B) with the residual |I - P|_F
-  kGramSym   // the same with a symmetric result
+  kGramSym   // the same with a symmetric result: upper tiles, mirrored
 };
 struct GemmJob {
   int m, n;
@@ -303,8 +311,8 @@ __device__ inline void gemm_tile(const GemmJob& g, const double* A, const double
 // BM/2 x 32 each as matrix-core tiles of 16 x 16.  The fp64 MFMA reads
 // op(A)(i, k) from lane i + 16 k and op(B)(k, j) from lane j + 16 k, and leaves
 // D(lane / 16 + 4 v, lane % 16) in element v of each lane (rows interleaved).
-// A product that is symmetric to first order in its operands' errors has only
-// the tiles that reach its upper triangle computed, and mirrored.
+// X^T X of the polar iteration, which is symmetric whatever X holds, has only the
+// tiles that reach its upper triangle computed, and mirrored.
 //
 // What bounds it: the fp64 matrix cores (78.6 TFLOP/s; the library reaches 72).
 // A 3072 x 3072 product takes 1.10 ms (53 TFLOP/s; 1.30 ms with 64 x 64 tiles and
@@ -328,7 +336,7 @@ __device__ __forceinline__ void gemm_batch(const GemmBatch& gb) {
     while (ji + 1 < gb.n_jobs && gb.first[ji + 1] <= t0) ++ji;
     const GemmJob& g = gb.job[ji];
     if (g.st && g.st->done) continue;
-    const bool sym = g.kind == kGramSym || g.kind == kStepSym;
+    const bool sym = g.kind == kGramSym;
     const long long t = t0 - gb.first[ji];
     const int ntn = (g.n + kBN - 1) / kBN;
     int tm, tn;
@@ -368,7 +376,7 @@ __device__ __forceinline__ void gemm_batch(const GemmBatch& gb) {
     }
 
     double alpha = g.alpha, beta = g.beta;
-    if (g.kind == kStep || g.kind == kStepSym) {
+    if (g.kind == kStep) {
       alpha = g.st->alpha;
       beta = g.st->beta;
     } else if (g.ratio_num) {
@@ -683,7 +691,7 @@ __device__ inline double ns_start_bound(double floor, double ridge) {
   return fmin(1.0, fmax(floor, sqrt(fmax(0.0, ridge))));
 }
 
-__device__ inline NsState ns_initial() {
+__device__ inline NsState ns_initial(double again) {
   NsState z;
   z.done = 0;
   z.extra = -1;
@@ -691,6 +699,7 @@ __device__ inline NsState ns_initial() {
   z.arrived = 0;
   z.res = -1.0;
   z.low = 1.0;
+  z.again = again;
   z.alpha = -0.5;
   z.beta = 1.5;
   return z;
@@ -706,8 +715,8 @@ __global__ __launch_bounds__(kRedThreads) void ns_start_kernel(const NsPair pr, 
   s = block_sum(s, red);
   if (threadIdx.x != 0) return;
   *q.lam = ridge * s / q.rows;
-  *q.st = ns_initial();
-  if (blockIdx.x == 0) *polar = ns_initial();
+  *q.st = ns_initial(1.0);
+  if (blockIdx.x == 0) *polar = ns_initial(kNsFloorPolar);
 }
 
 // *norm = |M + lam I|_F, and the singular value the scaled steps start from.
@@ -983,7 +992,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_roots_kernel(const NsPair
   if (tid == 0) {
     *q.lam = lam;
     *q.norm = c;
-    st = ns_initial();
+    st = ns_initial(1.0);
     st.low = ns_start_bound(q.floor, lam / c);
     ns_update(&st, res);
   }
@@ -993,24 +1002,23 @@ __global__ __launch_bounds__(kSmallThreads) void small_roots_kernel(const NsPair
     Z[1][e] = st.alpha * Y[0][e] + (i == j ? st.beta : 0.0);
   }
   {
-    SmallProduct g[1] = {small_product(d, d, d, Y[0], d, true, Y[0], d, true, Y[1], d)};
+    SmallProduct g[1] = {small_product(d, d, d, Y[0], d, false, Y[0], d, true, Y[1], d)};
     g[0].alpha = st.alpha;
     g[0].beta = st.beta;
     g[0].C = Y[0];
     g[0].ldc = d;
-    g[0].sym = true;
     small_products(g);
   }
   for (int it = 1; it < most; ++it) {
     const int a = it & 1, b = a ^ 1;
     {
-      const SmallProduct g[1] = {small_product(d, d, d, Z[a], d, true, Y[a], d, true, P, d)};
+      const SmallProduct g[1] = {small_product(d, d, d, Z[a], d, false, Y[a], d, true, P, d)};
       res = sqrt(total(small_products(g)));
     }
     if (tid == 0) ns_update(&st, res);
     __syncthreads();
     if (st.done) break;
-    SmallProduct g[2] = {small_product(d, d, d, Y[a], d, true, P, d, true, Y[b], d),
+    SmallProduct g[2] = {small_product(d, d, d, Y[a], d, false, P, d, true, Y[b], d),
                          small_product(d, d, d, P, d, false, Z[a], d, true, Z[b], d)};
 #pragma unroll
     for (int z = 0; z < 2; ++z) {
@@ -1018,7 +1026,6 @@ __global__ __launch_bounds__(kSmallThreads) void small_roots_kernel(const NsPair
       g[z].beta = st.beta;
       g[z].C = z ? Z[a] : Y[a];
       g[z].ldc = d;
-      g[z].sym = true;
     }
     small_products(g);
   }
@@ -1062,7 +1069,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_rest_kernel(const SmallRe
   const double* Zy = w.Zy[w.st[1].iters & 1];
   const double* Yy = w.Yy[w.st[1].iters & 1];
   {
-    const SmallProduct g[1] = {small_product(p, q, p, Zz, p, true, w.cov + p, pq, true, w.T1, q)};
+    const SmallProduct g[1] = {small_product(p, q, p, Zz, p, false, w.cov + p, pq, true, w.T1, q)};
     small_products(g);
   }
   {
@@ -1074,7 +1081,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_rest_kernel(const SmallRe
   const double inv = 1.0 / sqrt(total(s));
   for (int e = tid; e < p * q; e += kSmallThreads) w.X[0][e] *= inv;
   if (tid == 0) {
-    st = ns_initial();
+    st = ns_initial(kNsFloorPolar);
     st.low = ns_start_bound(kNsFloorPolar, 0.0);
   }
   __syncthreads();
@@ -1105,7 +1112,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_rest_kernel(const SmallRe
     small_products(g);
   }
   {
-    SmallProduct g[1] = {small_product(q, p, q, Yy, q, true, w.T2, p, true, w.A, p)};
+    SmallProduct g[1] = {small_product(q, p, q, Yy, q, false, w.T2, p, true, w.A, p)};
     g[0].alpha = sqrt(*w.cy / *w.cz);
     small_products(g);
   }
@@ -1226,7 +1233,7 @@ int grid_for(long long total, int threads = 256, int cap = 4096) {
 // upper triangle.
 long long tiles_of(const GemmJob& j, int bm) {
   const long long tm = (j.m + bm - 1) / bm, tn = (j.n + kBN - 1) / kBN;
-  const bool sym = j.kind == kGramSym || j.kind == kStepSym;
+  const bool sym = j.kind == kGramSym;
   return sym ? tm * tn - (bm / kBN) * (tm * (tm - 1) / 2) : tm * tn;
 }
 
@@ -1348,8 +1355,10 @@ struct Carve {
 
 // Steps after which an iteration is given up.  With the scaling, whatever 64 and
 // 128 plain steps bring to convergence (singular values down to 1e-10 and 7e-22
-// of the norm) takes at most 45 and 80.
-constexpr int kSqrtMaxIter = 48;
+// of the norm, in exact arithmetic) takes at most 60 and 80.  In fp64 the roots
+// converge up to condition numbers of about 1e14, as with plain steps: past that
+// rounding keeps |I - Z Y|_F from falling.
+constexpr int kSqrtMaxIter = 60;
 constexpr int kPolarMaxIter = 88;
 
 // Shares of a residual: one per tile of a d x d product, or one per workgroup of
@@ -1370,11 +1379,15 @@ struct RootBuffers {
 // side in the same launches:
 //   Y0 = S / c, Z0 = I, P = Z Y, Y <- beta Y + alpha Y P, Z <- beta Z + alpha P Z,
 // Y -> (S/c)^{1/2}, Z -> (S/c)^{-1/2}, with c = |S|_F.  Results in buffer
-// st->iters & 1.  With this order of the factors errors dY, dZ go over into
-// (dY - Y dZ Y) / 2 and (dZ - Z dY Z) / 2, which do not grow and are symmetric
-// as dY and dZ are: half of Y and Z is computed.  P is symmetric as well, but
-// its error dZ Y + Z dY is not, and taking it to be so (or Z P for P Z) makes
-// the iteration unstable (2.6e-8 instead of 1e-12 at 130 x 130): P is whole.
+// st->iters & 1.  Y, Z and P are symmetric in exact arithmetic, and none is taken to
+// be so: every product is whole, and reads its factors in this order and not
+// transposed.  Errors of Y and Z then go over into errors that do not grow; the
+// rounding of P, dZ Y + Z dY, is not symmetric, and a mirrored triangle of Y or Z, or
+// one read as its transpose, feeds that back.  |A S_Z A^T - S_Y| / |S_Y| at condition
+// numbers 1e4, 1e8, 1e12 of S_Y (150 x 140): 5e-15, 2e-13, 2e-11 as it is; 2e-14, 5e-11,
+// 5e-7 with Y and Z mirrored.  In fp64 on the host, Z read transposed doubles the error,
+// Y read transposed diverges at 1e12, and with Y alone mirrored the error is that of
+// whole products but one eigenvalue of 1e-14 no longer converges.
 hipError_t ns_roots(const NsPair& pr, const RootBuffers (&rb)[2], double ridge, NsState* polar,
                     GemmBatch* plan_ws, hipStream_t s) {
   Plan plan{plan_ws};
@@ -1396,18 +1409,18 @@ hipError_t ns_roots(const NsPair& pr, const RootBuffers (&rb)[2], double ridge, 
     for (int z = 0; z < 2; ++z) {
       const int d = pr.q[z].rows;
       if (gram) {
-        GemmJob& j = t.add(d, d, d, rb[z].Z[a], d, true, rb[z].Y[a], d, true, rb[z].P, d, kGram);
+        GemmJob& j = t.add(d, d, d, rb[z].Z[a], d, false, rb[z].Y[a], d, true, rb[z].P, d, kGram);
         j.st = pr.q[z].st;
         j.partial = pr.q[z].partial;
         continue;
       }
       const double* P = first ? rb[z].Y[0] : rb[z].P;
-      GemmJob& y = t.add(d, d, d, rb[z].Y[a], d, true, P, d, true, rb[z].Y[b], d, kStepSym);
+      GemmJob& y = t.add(d, d, d, rb[z].Y[a], d, false, P, d, true, rb[z].Y[b], d, kStep);
       y.C = rb[z].Y[a];
       y.ldc = d;
       y.st = pr.q[z].st;
       if (first) continue;  // Z1 is there
-      GemmJob& w = t.add(d, d, d, P, d, false, rb[z].Z[a], d, true, rb[z].Z[b], d, kStepSym);
+      GemmJob& w = t.add(d, d, d, P, d, false, rb[z].Z[a], d, true, rb[z].Z[b], d, kStep);
       w.C = rb[z].Z[a];
       w.ldc = d;
       w.st = pr.q[z].st;
@@ -1698,7 +1711,7 @@ hipError_t launch_recolor_solve(int p, int q, const double* mu, const double* co
   // M ~ Sigma_Z^{-1/2} Sigma_ZY Sigma_Y^{-1/2} (positive scale: the polar factor ignores it)
   {
     Batch t;
-    GemmJob& j = t.add(p, q, p, rb[0].Z[0], p, true, cov + p, pq, true, Tmp1, q);
+    GemmJob& j = t.add(p, q, p, rb[0].Z[0], p, false, cov + p, pq, true, Tmp1, q);
     j.a_sel = st;
     j.A1 = rb[0].Z[1];
     HF_CHECK(t.launch(s));
@@ -1723,7 +1736,7 @@ hipError_t launch_recolor_solve(int p, int q, const double* mu, const double* co
   }
   {
     Batch t;
-    GemmJob& j = t.add(q, p, q, rb[1].Y[0], q, true, Tmp2, p, true, A, p);
+    GemmJob& j = t.add(q, p, q, rb[1].Y[0], q, false, Tmp2, p, true, A, p);
     j.a_sel = st + 1;
     j.A1 = rb[1].Y[1];
     j.ratio_num = sc + kScCY;

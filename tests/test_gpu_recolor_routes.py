@@ -52,23 +52,82 @@ def test_solve_on_both_sides_of_the_one_workgroup_limit(hf, p, q):
     assert np.linalg.norm(_np(b) - b_ref) <= 1e-8 * (np.linalg.norm(b_ref) + np.linalg.norm(A_ref))
 
 
+def _with_root(rng, eig):
+    """(S, S^{1/2}) with the given eigenvalues in a random basis."""
+    U, _ = np.linalg.qr(rng.standard_normal((eig.size, eig.size)))
+    S = (U * eig) @ U.T
+    return 0.5 * (S + S.T), (U * np.sqrt(eig)) @ U.T
+
+
+def _solve(hf, Sz, Rz, Sy, Ry, W):
+    """A and the iteration record for the whitened cross-covariance W."""
+    C = Rz @ W @ Ry
+    cov = np.block([[Sz, C], [C.T, Sy]])
+    p = Sz.shape[0]
+    A, b, info = hf.hf_recolor_solve(_dev(np.zeros(cov.shape[0])), _dev(cov), p)
+    return _np(A), hf.recolor_info(info)
+
+
+def _cross(rng, p, q, sv):
+    """p x q with orthonormal factors and the given singular values; its polar factor."""
+    k = min(p, q)
+    U = np.linalg.qr(rng.standard_normal((p, k)))[0]
+    V = np.linalg.qr(rng.standard_normal((q, k)))[0]
+    return (U * sv) @ V.T, U @ V.T
+
+
+@pytest.mark.parametrize("kappa", [1e4, 1e8, 1e10, 1e12])
+@pytest.mark.parametrize("p,q", [(70, 60), (150, 140)])
+def test_solve_reproduces_an_ill_conditioned_receiver_covariance(hf, p, q, kappa):
+    # A S_Z A^T = S_Y, with S_Z of condition 10.  The coupled iteration leaves an
+    # error of about sqrt(kappa) eps in S_Y^{1/2} (0.1 to 0.2 of it in fp64 on the
+    # host, for plain and scaled steps); products and the other factors add tens of eps.
+    rng = np.random.default_rng(int(np.log10(kappa)) + p)
+    Sz, Rz = _with_root(rng, np.logspace(0, -1, p))
+    Sy, Ry = _with_root(rng, np.logspace(0, -np.log10(kappa), q))
+    W, _ = _cross(rng, p, q, np.linspace(1.0, 0.5, q))
+    A, inf = _solve(hf, Sz, Rz, Sy, Ry, W)
+    err = np.linalg.norm(A @ Sz @ A.T - Sy) / np.linalg.norm(Sy)
+    print(f"[gpu-recolor] S_Y kappa={kappa:.0e} p={p} q={q}: {err:.2e} {inf}", flush=True)
+    assert inf["converged"] == [1, 1, 1], inf
+    assert err <= (50 + 0.5 * np.sqrt(kappa)) * EPS
+
+
+@pytest.mark.parametrize("p,q", [(60, 12), (150, 20)])
+def test_roots_converge_with_one_eigenvalue_of_1e_14(hf, p, q):
+    rng = np.random.default_rng(p)
+    eig = np.ones(p)
+    eig[-1] = 1e-14
+    Sz, Rz = _with_root(rng, eig)
+    A, inf = _solve(hf, Sz, Rz, np.eye(q), np.eye(q), _cross(rng, p, q, np.ones(q))[0])
+    print(f"[gpu-recolor] one eigenvalue 1e-14, p={p}: {inf}", flush=True)
+    assert inf["converged"] == [1, 1, 1], inf
+
+
 @pytest.mark.parametrize("p,q", [(40, 8), (150, 20)])
-def test_solve_restarts_the_scaling_on_ill_conditioned_roots(hf, p, q):
-    # eigenvalues 1 .. 1e-12 of S_Z: plain steps need about 40 iterations, scaled
-    # ones go past their first schedule.  A S_Z A^T = S_Y holds to kappa eps.
+def test_solve_whitens_an_ill_conditioned_sender_covariance(hf, p, q):
+    # eigenvalues 1 .. 1e-12 of S_Z.  A S_Z A^T = S_Y = I holds to the error of
+    # S_Z^{-1/2}, at most half of kappa eps
     rng = np.random.default_rng(6)
-    U, _ = np.linalg.qr(rng.standard_normal((p, p)))
-    e = np.logspace(0, -12, p)
-    Sz = (U * e) @ U.T
-    Sz = 0.5 * (Sz + Sz.T)
-    G = (U * np.sqrt(e)) @ np.linalg.qr(rng.standard_normal((p, q)))[0]  # S_ZY of y = Q^T whitened z
-    cov = np.block([[Sz, G], [G.T, np.eye(q)]])
-    A, b, info = hf.hf_recolor_solve(_dev(np.zeros(p + q)), _dev(cov), p)
-    inf = hf.recolor_info(info)
-    print(f"[gpu-recolor] ill-conditioned p={p}: {inf}", flush=True)
-    assert inf["converged"][0] == 1 and inf["iterations"][0] > 20, inf
-    Am = _np(A)
-    assert np.linalg.norm(Am @ Sz @ Am.T - np.eye(q)) <= 1e12 * EPS * 100
+    Sz, Rz = _with_root(rng, np.logspace(0, -12, p))
+    A, inf = _solve(hf, Sz, Rz, np.eye(q), np.eye(q), _cross(rng, p, q, np.ones(q))[0])
+    err = np.linalg.norm(A @ Sz @ A.T - np.eye(q))
+    print(f"[gpu-recolor] S_Z kappa=1e12 p={p}: {err:.2e} {inf}", flush=True)
+    assert inf["converged"] == [1, 1, 1] and inf["iterations"][0] > 20, inf
+    assert err <= 0.5 * 1e12 * EPS
+
+
+@pytest.mark.parametrize("p,q", [(60, 40), (40, 60), (150, 140), (140, 150)])
+def test_polar_iteration_restarts_its_scaling(hf, p, q):
+    # singular values 1 .. 1e-8 of the whitened cross-covariance, past the first
+    # schedule of scaled steps; the polar factor is accurate to kappa eps
+    rng = np.random.default_rng(p + q)
+    W, R = _cross(rng, p, q, np.logspace(0, -8, min(p, q)))
+    A, inf = _solve(hf, np.eye(p), np.eye(p), np.eye(q), np.eye(q), W)
+    err = np.linalg.norm(A - R.T) / np.linalg.norm(R)
+    print(f"[gpu-recolor] polar p={p} q={q}: {err:.2e} {inf}", flush=True)
+    assert inf["converged"] == [1, 1, 1] and inf["iterations"][2] > 20, inf
+    assert err <= 1e8 * EPS * 10
 
 
 @pytest.mark.parametrize("ak,bk", [(False, True), (True, True), (False, False), (True, False)])
