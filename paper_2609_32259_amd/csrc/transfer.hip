@@ -142,6 +142,36 @@ __device__ __forceinline__ Ctx make_ctx(const TransferArgs& p, const Item& it, i
   return x;
 }
 
+// One entry added to a row's sums: x[u] and x[u + 8] from the taps' features
+// (lo: l0, l1; hi: h0, h1), with the layer weights a, bq times the entry's own, and
+// for keys the rotation U(p_i) of the pair.  Every operation rounds as written: the
+// callers have branches in different places, and what the compiler would fuse (a
+// product into a later sum) would depend on them.
+__device__ __forceinline__ void add_entry(float* x, const uint4& L0, const uint4& L1,
+                                          const uint4& H0, const uint4& H1, float a, float bq,
+                                          bool two_tap, bool unrot, const float* cc,
+                                          const float* ss) {
+#pragma clang fp contract(off)
+  const uint32_t l0[4] = {L0.x, L0.y, L0.z, L0.w}, l1[4] = {L1.x, L1.y, L1.z, L1.w};
+  const uint32_t h0[4] = {H0.x, H0.y, H0.z, H0.w}, h1[4] = {H1.x, H1.y, H1.z, H1.w};
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    float ma = a * ((u & 1) ? bf_hi(l0[u >> 1]) : bf_lo(l0[u >> 1]));
+    float mb = a * ((u & 1) ? bf_hi(l1[u >> 1]) : bf_lo(l1[u >> 1]));
+    if (two_tap) {
+      ma = fmaf(bq, (u & 1) ? bf_hi(h0[u >> 1]) : bf_lo(h0[u >> 1]), ma);
+      mb = fmaf(bq, (u & 1) ? bf_hi(h1[u >> 1]) : bf_lo(h1[u >> 1]), mb);
+    }
+    if (unrot) {  // U(p) = R(-p) on the pair (e0 + u, e0 + 64 + u)
+      x[u] = fmaf(ma, cc[u], fmaf(mb, ss[u], x[u]));
+      x[u + 8] = fmaf(mb, cc[u], fmaf(-ma, ss[u], x[u + 8]));
+    } else {
+      x[u] += ma;
+      x[u + 8] += mb;
+    }
+  }
+}
+
 // Accumulate the aligned features of one receiver row straight from global
 // memory: x[0..7] = features e0..e0+7 and x[8..15] = e0+64..e0+71 of sender
 // head h (a RoPE pair per index).  Used where the staged path does not apply.
@@ -161,8 +191,6 @@ __device__ __forceinline__ void build_row_global(const TransferArgs& p, const Ct
       H1 = *reinterpret_cast<const uint4*>(cx.S_hi + off + 64);
     }
     const float a = w * cx.wlo, bq = w * cx.whi;
-    const uint32_t l0[4] = {L0.x, L0.y, L0.z, L0.w}, l1[4] = {L1.x, L1.y, L1.z, L1.w};
-    const uint32_t h0[4] = {H0.x, H0.y, H0.z, H0.w}, h1[4] = {H1.x, H1.y, H1.z, H1.w};
     float cc[8], ss[8];
     if (cx.cs_s) {
       const float* row = cx.cs_s + (long long)i * kDH;
@@ -175,22 +203,7 @@ __device__ __forceinline__ void build_row_global(const TransferArgs& p, const Ct
       ss[0] = s0.x; ss[1] = s0.y; ss[2] = s0.z; ss[3] = s0.w;
       ss[4] = s1.x; ss[5] = s1.y; ss[6] = s1.z; ss[7] = s1.w;
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      float ma = a * ((u & 1) ? bf_hi(l0[u >> 1]) : bf_lo(l0[u >> 1]));
-      float mb = a * ((u & 1) ? bf_hi(l1[u >> 1]) : bf_lo(l1[u >> 1]));
-      if (cx.two_tap) {
-        ma = fmaf(bq, (u & 1) ? bf_hi(h0[u >> 1]) : bf_lo(h0[u >> 1]), ma);
-        mb = fmaf(bq, (u & 1) ? bf_hi(h1[u >> 1]) : bf_lo(h1[u >> 1]), mb);
-      }
-      if (cx.cs_s) {  // U(p) = R(-p) on the pair (e0 + u, e0 + 64 + u)
-        x[u] = fmaf(ma, cc[u], fmaf(mb, ss[u], x[u]));
-        x[u + 8] = fmaf(mb, cc[u], fmaf(-ma, ss[u], x[u + 8]));
-      } else {
-        x[u] += ma;
-        x[u + 8] += mb;
-      }
-    }
+    add_entry(x, L0, L1, H0, H1, a, bq, cx.two_tap, cx.cs_s != nullptr, cc, ss);
   }
 }
 
@@ -243,7 +256,7 @@ __device__ __forceinline__ void scale_by_weights(float (*y)[16], const int* feat
 // token of the lane group's run: the small-offset rotations U(0..15) sit in
 // LDS and U(q_g) is applied once to each row's sum.  Tiles whose entry count or
 // run sender span exceed what is staged build X entry by entry from the CSR
-// and the full RoPE table in global memory (same results).
+// and the full RoPE table in global memory.
 // ---------------------------------------------------------------------------
 constexpr int kEMax = 512;             // CSR entries staged per tile
 constexpr int kDMax = kRopeDeltaRows;  // in-row sender offsets handled with the LDS table
@@ -278,6 +291,11 @@ static_assert(kSmemBytes <= 160 * 1024, "LDS budget");
 // use an out-of-range buffer offset, which returns zeros without touching
 // memory, so every trip issues the same loads and a ring of R trips keeps
 // R - 1 trips of loads in flight.
+// ABS (the kernels that stage their tiles themselves): each entry is rotated by its
+// own U(p_i) from the table, and added by add_entry, so that the results are those of
+// build_row_global bit for bit.  The split rotation differs in the last bits of fp32,
+// which moves 0.2% of the bf16 results; it is 1 to 4% faster (8 -> 2 heads, 1,821 rows:
+// 198 against 202 us; 14,250 rows: 1,300 against 1,361).
 constexpr int kOOB = (int)0x80000000;  // buffer offset past any slab extent (extents < 2^31)
 
 struct GroupLds {
@@ -289,9 +307,10 @@ struct GroupLds {
   int e_base;
 };
 
-template <bool TWO_TAP>
+template <bool TWO_TAP, bool ABS>
 struct Trip {
   uint4 a0, a1, b0, b1;  // tap lo / hi: features e0..e0+7 and e0+64..e0+71
+  uint4 c0, c1, s0, s1;  // ABS: U(p_i) of features e0..e0+7 (cos, sin)
   int code;              // -1: no entry; else row | last << 6 | (i - base) << 8
   float w;
 };
@@ -322,7 +341,7 @@ struct LdsSink {  // the X tile in LDS (row stride kXF)
   }
 };
 
-template <bool TWO_TAP, bool UNROT, int R, class Sink>
+template <bool TWO_TAP, bool UNROT, bool ABS, int R, class Sink>
 __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& p, const GroupLds& L,
                                              int base, int src_head, int head, int r_first, int rpg,
                                              int lane, const Sink& sink) {
@@ -340,7 +359,7 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
     }
   }
   float rc[8], rs[8];  // U(p_base): closes every row of the group
-  if (UNROT) {
+  if (UNROT && !ABS) {
     const float* row = cx.cs_s + (long long)base * kDH;
     const float4 c0 = *reinterpret_cast<const float4*>(row + e0);
     const float4 c1 = *reinterpret_cast<const float4*>(row + e0 + 4);
@@ -355,15 +374,17 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
       __builtin_amdgcn_make_buffer_rsrc((void*)cx.S_lo, 0, p.s_extent, 0x00020000);
   const __amdgpu_buffer_rsrc_t rhi =
       __builtin_amdgcn_make_buffer_rsrc((void*)cx.S_hi, 0, p.s_extent, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rcs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)cx.cs_s, 0, cx.Ts * kDH * 4, 0x00020000);
   const int hoff = (int)(src_head * p.s_sh + e0) * 2;  // bytes
   const int tstride = (int)p.s_st * 2;
 
-  Trip<TWO_TAP> ring[R];
+  Trip<TWO_TAP, UNROT && ABS> ring[R];
   float x[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) x[u] = 0.0f;
 
-  auto issue = [&](Trip<TWO_TAP>& t, int k) {
+  auto issue = [&](Trip<TWO_TAP, UNROT && ABS>& t, int k) {
     const bool valid = k < E;
     int i = 0, info = 0;
     float w = 0.0f;
@@ -379,10 +400,17 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
       t.b0 = buf_load16(rhi, off);
       t.b1 = buf_load16(rhi, off + 128);
     }
-    t.code = valid ? ((info & 63) | ((info >> 8) << 6) | ((UNROT ? i - base : 0) << 8)) : -1;
+    if (UNROT && ABS) {
+      const int co = valid ? i * (kDH * 4) + e0 * 4 : kOOB;  // fewer than 2^22 sender rows
+      t.c0 = buf_load16(rcs, co);
+      t.c1 = buf_load16(rcs, co + 16);
+      t.s0 = buf_load16(rcs, co + 256);
+      t.s1 = buf_load16(rcs, co + 272);
+    }
+    t.code = valid ? ((info & 63) | ((info >> 8) << 6) | ((UNROT && !ABS ? i - base : 0) << 8)) : -1;
     t.w = w;
   };
-  auto consume = [&](const Trip<TWO_TAP>& t) {
+  auto consume = [&](const Trip<TWO_TAP, UNROT && ABS>& t) {
     if (t.code < 0) return;
     const uint32_t l0[4] = {t.a0.x, t.a0.y, t.a0.z, t.a0.w};
     const uint32_t l1[4] = {t.a1.x, t.a1.y, t.a1.z, t.a1.w};
@@ -393,7 +421,22 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
     }
     const float a = t.w * cx.wlo, bq = t.w * cx.whi;  // weight folded into the layer mix
     float cc[8], ss[8];
-    if (UNROT) table_row(L.dt, t.code >> 8, e0, cc, ss);  // U(p_i - p_base)
+    if (UNROT && !ABS) table_row(L.dt, t.code >> 8, e0, cc, ss);  // U(p_i - p_base)
+    if (ABS && UNROT) {
+      const uint4 v[4] = {t.c0, t.c1, t.s0, t.s1};
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float* d = (g < 2 ? cc : ss) + 4 * (g & 1);
+        d[0] = __uint_as_float(v[g].x);
+        d[1] = __uint_as_float(v[g].y);
+        d[2] = __uint_as_float(v[g].z);
+        d[3] = __uint_as_float(v[g].w);
+      }
+    }
+    if (ABS) {
+      const uint4 z = make_uint4(0, 0, 0, 0);
+      add_entry(x, t.a0, t.a1, TWO_TAP ? t.b0 : z, TWO_TAP ? t.b1 : z, a, bq, TWO_TAP, UNROT, cc, ss);
+    } else {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       float ma = a * ((u & 1) ? bf_hi(l0[u >> 1]) : bf_lo(l0[u >> 1]));
@@ -410,8 +453,9 @@ __device__ __forceinline__ void build_groups(const Ctx& cx, const TransferArgs& 
         x[u + 8] += mb;
       }
     }
+    }
     if ((t.code >> 6) & 1) {  // last entry of the row: close the rotation, round, store
-      if (UNROT) {
+      if (UNROT && !ABS) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const float a = x[u], b = x[u + 8];
@@ -644,7 +688,7 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   }
   if (OWN) stage_tile(p, item % p.tiles_per_lc, estart);
   else copy_record(item);
-  if (p.unrot) {  // U(0..15): rows 0..15 of the sender table, 2 per wave
+  if (!OWN && p.unrot) {  // U(0..15): rows 0..15 of the sender table, 2 per wave
     const int ri = wave * 2 + (lane >> 5);
     const int c = (lane & 31) ^ (ri & 1);
     copy16_to_lds(p.cs_s + (long long)ri * kDH + 4 * c, dt + wave * 2 * kDH);
@@ -661,7 +705,8 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   const int g0 = p.row0[it.b] + j0;
   const bool unrot = cx.cs_s != nullptr;
   const int e_base = estart[0];
-  const bool staged = p.s_extent > 0 && flag[1] == 0 && !(unrot && flag[0] != 0);
+  const bool staged = p.s_extent > 0 && flag[1] == 0 &&
+                      !(unrot && (OWN ? cx.Ts >= (1 << 22) : flag[0] != 0));
   int grabbed = n_items;
   if (kPersist && tid == 0) grabbed = next_item_of(p, queue, n_items);
 
@@ -691,7 +736,9 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
     const int KS = Hp * (kDH / 16);                    // and its k-steps
     // The first one.  In plain order, where all workgroups share a map, they start at
     // different sender heads; an XCD's few start at the same one and meet in its L2.
-    const int ks0 = (int)((unsigned)(p.n_queues > 1 ? lc_store : item) % (unsigned)Hp) * (kDH / 16);
+    // OWN: all at the first, so that a result does not depend on the work order.
+    const int ks0 =
+        OWN ? 0 : (int)((unsigned)(p.n_queues > 1 ? lc_store : item) % (unsigned)Hp) * (kDH / 16);
     const Ctx ct = make_ctx(p, it, tap);
     // ---- build X[64][Hp d_h] of this pass ----
     if (staged) {
@@ -705,26 +752,30 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
         const int base = gbase[grp];
         const int src = h_first + sh;
         auto build = [&](auto two, auto rotate, auto ring) {
-          build_groups<decltype(two)::value, decltype(rotate)::value, decltype(ring)::value>(
+          build_groups<decltype(two)::value, decltype(rotate)::value, OWN, decltype(ring)::value>(
               ct, p, L, base, src, sh, r_first, rpg, lane, xsink);
         };
         using T = std::true_type;
         using F = std::false_type;
         using R3 = std::integral_constant<int, 3>;
         using R2 = std::integral_constant<int, 2>;
-        // two receiver heads leave registers for the deeper ring in every pass
+        // Trips in flight in the first pass and the later ones.  Two receiver heads
+        // leave registers for the deeper ring in every pass; eight with the entries'
+        // own rotations in none (16 -> 8 heads, 1,821 rows: 685 us with 53 registers
+        // spilled, 647 with 3).
+        using R0 = std::conditional_t<OWN && HR == 8, R2, R3>;
         using Rn = std::conditional_t<HR == 2, R3, R2>;
         if ((!MULTI || OWN) && ct.two_tap) {  // concatenated taps are one sender layer each
           if (!MULTI || pass == 0) {
-            if (unrot) build(T(), T(), R3());
-            else build(T(), F(), R3());
+            if (unrot) build(T(), T(), R0());
+            else build(T(), F(), R0());
           } else {
             if (unrot) build(T(), T(), Rn());
             else build(T(), F(), Rn());
           }
         } else if (!MULTI || pass == 0) {
-          if (unrot) build(F(), T(), R3());
-          else build(F(), F(), R3());
+          if (unrot) build(F(), T(), R0());
+          else build(F(), F(), R0());
         } else {
           if (unrot) build(F(), T(), Rn());
           else build(F(), F(), Rn());
@@ -1003,10 +1054,10 @@ __global__ __launch_bounds__(512) void staged_build_kernel(const TransferArgs p)
     const GroupLds L{estart, ecol, ew, einfo, dt, estart[0]};
     const int grp = lane >> 3;
     const int r_first = gstart[grp], rpg = gstart[grp + 1] - r_first, base = gbase[grp];
-    if (cx.two_tap && unrot) build_groups<true, true, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
-    else if (cx.two_tap) build_groups<true, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
-    else if (unrot) build_groups<false, true, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
-    else build_groups<false, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    if (cx.two_tap && unrot) build_groups<true, true, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    else if (cx.two_tap) build_groups<true, false, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    else if (unrot) build_groups<false, true, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
+    else build_groups<false, false, false, 3>(cx, p, L, base, wave, wave, r_first, rpg, lane, sink);
     // The wave's own head (k-tiles 4 wave .. 4 wave + 3 of the 64 rows) goes
     // out as soon as its walk ends: LDS operations of one wave run in order.
     const int c8 = (lane & 3) * 8;
