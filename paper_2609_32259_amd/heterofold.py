@@ -251,6 +251,8 @@ def hf_build_alignment(s_cu, r_cu, s_beg, s_end, r_beg, r_end, mode="overlap",
     host prefix sums.  Returns the CSR table (allocated unless ``out``)."""
     torch = _torch()
     s_cu, r_cu = _i32(s_cu), _i32(r_cu)
+    if s_cu.size != r_cu.size:
+        raise ValueError("s_cu and r_cu differ in length")
     B = s_cu.size - 1
     dev = s_beg.device
     if out is None:

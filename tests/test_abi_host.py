@@ -121,6 +121,18 @@ def _desc(ptr=0x1000, dtype=1, L_=4, H=8, d=128, T=64):
     return hf.hf_kv_desc(C.c_void_p(ptr), dtype, L_, H, d, T, st_b, st_l, st_c, st_h, st_t)
 
 
+def test_alignment_prefix_sums_of_different_lengths_are_refused(L):
+    # also with the table and the workspace given, where no size is queried
+    import torch
+    z = torch.zeros(8, dtype=torch.int32)
+    s_cu, r_cu = np.array([0, 2, 4], np.int32), np.array([0, 3], np.int32)
+    out = hf.Alignment(z, z, z, z, s_cu, r_cu)
+    ws = torch.zeros(256, dtype=torch.uint8)
+    for table in (None, out):
+        with pytest.raises(ValueError, match="differ in length"):
+            hf.hf_build_alignment(s_cu, r_cu, z, z, z, z, out=table, workspace=ws)
+
+
 def test_transfer_host_validation(L):
     s_len = np.array([64], np.int32)
     r_len = np.array([60], np.int32)
