@@ -68,14 +68,16 @@ def algorithmic_cost(cfg, seg):
     return flops, read + write + maps
 
 
-def kernel_name(cfg):
-    """The transfer kernel hf_transfer_kv(_taps) launches for this shape."""
+def kernel_name(cfg, r_len):
+    """The transfer kernel hf_transfer_kv(_taps) launches for this shape and batch."""
     if cfg.dtype != "bf16":
         return "transfer_f32_kernel"
     records = cfg.H_r in (4, 8) and cfg.H_s <= 8
     tf = lambda b: "true" if b else "false"  # noqa: E731
-    return (f"transfer_bf16_tiled_kernel<{cfg.H_r}, {tf(cfg.n_taps > 1 or cfg.H_s > 8)}, "
-            f"{tf(not records)}>")
+    multi = cfg.n_taps > 1 or cfg.H_s > 8
+    queued = records and not multi and sum(-(-int(t) // 64) for t in r_len) <= 128
+    return (f"transfer_bf16_tiled_kernel<{cfg.H_r}, {tf(multi)}, {tf(not records)}, "
+            f"{tf(queued)}>")
 
 
 def kernel_traffic(cfg, staged=False):
@@ -493,7 +495,7 @@ def main():
     roof = {"bound": bound, "achieved": round(achieved, 2), "peak": peak,
             "unit": unit, "frac": round(achieved / peak, 4), "traffic": traffic,
             "tflops": round(flops / (k_avg * 1e-3) / 1e12, 2), "algorithmic_flops": flops,
-            "kernel": "staged_gemm_kernel" if ran_staged else kernel_name(cfg),
+            "kernel": "staged_gemm_kernel" if ran_staged else kernel_name(cfg, wl.seg.r_len),
             "kernel_ms": round(k_avg, 4),
             "kernel_ms_median": round(k_med, 4), "kernel_ms_min": round(k_min, 4),
             "kernel_ms_p90": round(k_p90, 4),

@@ -52,8 +52,8 @@ struct TransferArgs {
   const int32_t* num;
   const int32_t* den;
   const int32_t* tile_rec;  // per-row-tile staging records (tiled bf16 kernel)
-  int32_t* work_ctr;        // next work item of each queue (persistent tiled kernel)
-  int32_t n_queues;         // queues the tiled kernel's work items are dealt in
+  int32_t* work_ctr;        // next work item, or next of each queue (persistent tiled kernel)
+  int32_t queued;           // 1: the tiled kernel's work items are dealt in queues
   int32_t n_wg;             // workgroups of the persistent tiled kernel
   const float* cs_s;    // sender RoPE table [P_s][d_h]: cos of the d_h/2 angles, then sin
   const float* cs_r;    // receiver RoPE table [P_r][d_h], same layout
@@ -109,7 +109,7 @@ int transfer_f32_rows_per_tile(int H_s, int n_taps, int d_h);
 // Device bytes of the staging record each row tile needs (0 where the kernel
 // that runs keeps no records).
 size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h);
-// Sets a.n_queues (after the tiles and layers are set).
+// Sets a.queued (after the tiles and layers are set).
 void transfer_order(TransferArgs& a);
 // Workgroups of the persistent tiled kernel on a device with n_cu compute units.
 int transfer_persistent_grid(const TransferArgs& a, int n_cu);

@@ -573,26 +573,27 @@ __device__ __forceinline__ void stage_tile(const TransferArgs& p, int t, int* en
   __syncthreads();
 }
 
-// Work items in p.n_queues queues; workgroup i takes queue i % n_queues.  One queue
-// is the plain order.  With eight, queue q holds the tiles of every eighth (layer,
-// role) from q on: workgroup i runs on XCD i % 8, so the workgroups of an XCD share
-// one map in its L2 (transfer_queues says when).
-constexpr int kMaxQueues = 8;
+// Work items in plain order, or dealt in kQueues queues (transfer_order says when):
+// queue q then holds the tiles of every eighth (layer, role) from q on.  Workgroup i
+// takes from queue i % 8 and runs on XCD i % 8, so the workgroups of an XCD share one
+// map in its L2.
+constexpr int kQueues = 8;
 constexpr int kCtrStride = 8;  // ints between the queues' counters (256 bytes in all)
 constexpr int kCtrTotal = 4;   // the count of all items taken, between the first two
 
 __device__ __forceinline__ int queue_items(const TransferArgs& p, int q) {
-  return p.tiles_per_lc * ((2 * p.L_r - q + p.n_queues - 1) / p.n_queues);
+  return p.tiles_per_lc * ((2 * p.L_r - q + kQueues - 1) / kQueues);
 }
 // Item v of queue q, in plain order.
 __device__ __forceinline__ int queue_item(const TransferArgs& p, int q, int v) {
   const int i = v / p.tiles_per_lc;
-  return (p.n_queues * i + q) * p.tiles_per_lc + (v - i * p.tiles_per_lc);
+  return (kQueues * i + q) * p.tiles_per_lc + (v - i * p.tiles_per_lc);
 }
 // An item of the queues after `own` (which is empty), or n_items if they are too.
 __device__ __forceinline__ int other_queue_item(const TransferArgs& p, int own, int n_items) {
-  for (int i = 1; i < p.n_queues; ++i) {
-    const int q = (own + i) % p.n_queues, n = queue_items(p, q);
+#pragma unroll 1
+  for (int i = 1; i < kQueues; ++i) {
+    const int q = (own + i) % kQueues, n = queue_items(p, q);
     if (n <= 0) continue;
     const int v = atomicAdd(p.work_ctr + q * kCtrStride, 1);
     if (v < n) return queue_item(p, q, v);
@@ -617,9 +618,10 @@ __global__ __launch_bounds__(512) void prologue_kernel(const TransferArgs p, int
   __shared__ __attribute__((aligned(16))) int ent[kRecBytes / 4];
   int blk = blockIdx.x;
   if (blk < n_stage) {
-    if (blk == 0 && (int)threadIdx.x < p.n_queues) {  // a queue's first items start statically
-      const int q = threadIdx.x, wgs = (p.n_wg - q + p.n_queues - 1) / p.n_queues;
-      p.work_ctr[q * kCtrStride] = min(wgs, queue_items(p, q));
+    if (blk == 0 && threadIdx.x < kQueues) {  // the first items are taken statically
+      const int q = threadIdx.x, wgs = (p.n_wg - q + kQueues - 1) / kQueues;
+      if (p.queued) p.work_ctr[q * kCtrStride] = min(wgs, queue_items(p, q));
+      else if (q == 0) p.work_ctr[0] = p.n_wg;
       if (q == 0) p.work_ctr[kCtrTotal] = p.n_wg;
     }
     stage_tile(p, blk, ent);
@@ -640,8 +642,12 @@ __global__ __launch_bounds__(512) void prologue_kernel(const TransferArgs p, int
 // HR: receiver heads.  MULTI: several passes over the X tile (concatenated taps,
 // or more than kHMax sender heads).  OWN: the call's workspace has no records
 // and no work counter (two receiver heads, or more than kHMax sender heads), so
-// every workgroup does one item and stages its tile itself.
-template <int HR, bool MULTI, bool OWN>
+// every workgroup does one item and stages its tile itself.  QUEUED: a persistent
+// workgroup takes its items from the queues (the others map their one item with
+// p.queued).  A kernel of its own for the plain order: with the queues' search in it
+// the 8 -> 4-head kernel has 68 bytes of scratch a lane instead of none, and calls of
+// 32K tokens take 0.5 to 0.8% longer.
+template <int HR, bool MULTI, bool OWN, bool QUEUED>
 __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const TransferArgs p) {
   constexpr int NTW = HR == 8 ? 4 : 2;  // 32-feature tiles per wave
   constexpr int MT = HR == 2 ? 1 : 2;   // 32-row blocks per wave
@@ -669,22 +675,26 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
     copy16_to_lds(rec + wave * 256 + 4 * lane, estart + wave * 256);
   };
 
-  // Persistent (interpolating map): the workgroup starts on item blockIdx.x / n_queues
-  // of its queue and takes the next one from the queue's counter (set to the
-  // queue's workgroups by the prologue) while it builds, so the items in flight stay
-  // a contiguous run of each queue, and the next record is copied in during the
-  // store.  With several passes (which leave no registers for the loop) a
-  // workgroup does one item.
+  // Persistent (interpolating map): the workgroup starts on item blockIdx.x, or item
+  // blockIdx.x / 8 of its queue, and takes the next one from the counter (set to the
+  // items started this way by the prologue) while it builds, so the items in flight
+  // stay a contiguous run of the order or of each queue, and the next record is copied
+  // in during the store.  With several passes (which leave no registers for the loop)
+  // a workgroup does one item, and the queues are equally long.
   constexpr bool kPersist = !MULTI && !OWN;
-  const int queue = blockIdx.x % p.n_queues, first = blockIdx.x / p.n_queues;
-  int item;
-  if (!kPersist || first < queue_items(p, queue)) {
-    item = queue_item(p, queue, first);  // without the loop, the queues are equally long
-  } else {  // more workgroups than items in this queue
-    if (tid == 0) *next_item = other_queue_item(p, queue, n_items);
-    __syncthreads();
-    item = *next_item;
-    if (item >= n_items) return;
+  const int queue = blockIdx.x % kQueues, first = blockIdx.x / kQueues;
+  int item = blockIdx.x;
+  if (!kPersist) {
+    if (p.queued) item = queue_item(p, queue, first);
+  } else if (QUEUED) {
+    if (first < queue_items(p, queue)) {
+      item = queue_item(p, queue, first);
+    } else {  // more workgroups than items in this queue
+      if (tid == 0) *next_item = other_queue_item(p, queue, n_items);
+      __syncthreads();
+      item = *next_item;
+      if (item >= n_items) return;
+    }
   }
   if (OWN) stage_tile(p, item % p.tiles_per_lc, estart);
   else copy_record(item);
@@ -708,7 +718,8 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
   const bool staged = p.s_extent > 0 && flag[1] == 0 &&
                       !(unrot && (OWN ? cx.Ts >= (1 << 22) : flag[0] != 0));
   int grabbed = n_items;
-  if (kPersist && tid == 0) grabbed = next_item_of(p, queue, n_items);
+  if (kPersist && tid == 0)
+    grabbed = QUEUED ? next_item_of(p, queue, n_items) : atomicAdd(p.work_ctr, 1);
 
   f32x16 acc[MT][NTW];  // zeroed after the first pass's build
   // This wave's accumulators: receiver head `head`, n-tiles feat[q].
@@ -738,7 +749,9 @@ __global__ __launch_bounds__(512, 1) void transfer_bf16_tiled_kernel(const Trans
     // different sender heads; an XCD's few start at the same one and meet in its L2.
     // OWN: all at the first, so that a result does not depend on the work order.
     const int ks0 =
-        OWN ? 0 : (int)((unsigned)(p.n_queues > 1 ? lc_store : item) % (unsigned)Hp) * (kDH / 16);
+        OWN ? 0
+            : (int)((unsigned)((kPersist ? QUEUED : p.queued != 0) ? lc_store : item) %
+                    (unsigned)Hp) * (kDH / 16);
     const Ctx ct = make_ctx(p, it, tap);
     // ---- build X[64][Hp d_h] of this pass ----
     if (staged) {
@@ -1101,20 +1114,25 @@ size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h) {
   return uses_records(dtype, H_r, H_s, d_h) ? kRecBytes : 0;
 }
 
-// Eight queues up to kQueueTiles row tiles, one past that.  In plain order the tiles
-// of a (layer, role) lie on all XCDs and each fetches the 2 MB map: of a 200-token
-// message's 92 us, 64 were that stream.  Kernel us in plain order, in eight queues,
-// and in eight queues with one start of the k-loop per map (32 -> 40 layers, 8 -> 8
-// heads): 200 tokens 93/86/61, 500 195/165/140, 1K 318/252/244, 2K 542/439/443, 4K
-// 897/852/843, 8K 1649/1638/1626; at 16K (229 tiles) 3166/3207/3175, at 32K one
-// queue is 1% faster.  8 -> 4 heads, 4K: 393/369/375.
+// In queues up to kQueueTiles row tiles, in plain order past that.  In plain order the
+// tiles of a (layer, role) lie on all XCDs and each fetches the map (2 MB for 8 -> 8
+// heads, half that for 8 -> 4 and 4 -> 8).  Queued over plain kernel time at 3, 7, 14,
+// 28, 56, 78, 100, 125, 167 and 223 tiles (200 to 16K tokens):
+//   8 -> 8         .59 .69 .76 .81 .93 .97 .99 .98 1.00 1.00  (93 -> 55 us at 3 tiles)
+//   8 -> 4         .74 .71 .90 .96 1.00 .98 1.00 .98 1.00 .99
+//   4 -> 8         .70 .71 .86 .94 1.00 1.00 1.03 .99 1.01 1.01
+//   2 -> 4         .83 .94 .98 .98 .98 .98 1.02 1.02 1.03 1.01
+//   8 -> 4, 3 taps .74 .60 .81 .99 .99 1.00 1.03 1.00 1.00 .98
+//   8 -> 2         .96 .89 .97 1.02 1.01 1.00 1.01 1.00 1.02 1.01
+//   16 -> 8        .76 .63 .78 .90 .95 .97
+// so the line lies where the largest map stops gaining; runs differ by 1 to 2%.
 // A kernel of one item per workgroup needs queues of one length.
 constexpr int kQueueTiles = 128;
 
 void transfer_order(TransferArgs& a) {
   const bool one_each = a.concat || a.H_s > kHMax || !uses_records(HF_BF16, a.H_r, a.H_s, a.d_h);
-  const bool even = 2 * a.L_r % kMaxQueues == 0;
-  a.n_queues = a.tiles_per_lc <= kQueueTiles && (even || !one_each) ? kMaxQueues : 1;
+  const bool even = 2 * a.L_r % kQueues == 0;
+  a.queued = a.tiles_per_lc <= kQueueTiles && (even || !one_each);
 }
 
 int transfer_persistent_grid(const TransferArgs& a, int n_cu) {
@@ -1220,19 +1238,24 @@ hipError_t launch_transfer(int dtype, const TransferArgs& a, hipStream_t s) {
   const dim3 block(512);
   if (dtype == HF_BF16) {
     const bool multi = a.concat || a.H_s > kHMax;  // several passes over the X tile
+#define HF_TILED(GRID, ...) \
+  hipLaunchKernelGGL((transfer_bf16_tiled_kernel<__VA_ARGS__>), GRID, block, 0, s, a)
     if (rec && a.H_r == 8) {
-      if (multi) hipLaunchKernelGGL((transfer_bf16_tiled_kernel<8, true, false>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((transfer_bf16_tiled_kernel<8, false, false>), pgrid, block, 0, s, a);
+      if (multi) HF_TILED(grid, 8, true, false, false);
+      else if (a.queued) HF_TILED(pgrid, 8, false, false, true);
+      else HF_TILED(pgrid, 8, false, false, false);
     } else if (rec) {
-      if (multi) hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, true, false>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, false, false>), pgrid, block, 0, s, a);
+      if (multi) HF_TILED(grid, 4, true, false, false);
+      else if (a.queued) HF_TILED(pgrid, 4, false, false, true);
+      else HF_TILED(pgrid, 4, false, false, false);
     } else if (a.H_r == 8) {
-      hipLaunchKernelGGL((transfer_bf16_tiled_kernel<8, true, true>), grid, block, 0, s, a);
+      HF_TILED(grid, 8, true, true, false);
     } else if (a.H_r == 4) {
-      hipLaunchKernelGGL((transfer_bf16_tiled_kernel<4, true, true>), grid, block, 0, s, a);
+      HF_TILED(grid, 4, true, true, false);
     } else if (a.H_r == 2) {
-      if (multi) hipLaunchKernelGGL((transfer_bf16_tiled_kernel<2, true, true>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((transfer_bf16_tiled_kernel<2, false, true>), grid, block, 0, s, a);
+      if (multi) HF_TILED(grid, 2, true, true, false);
+      else HF_TILED(grid, 2, false, true, false);
+#undef HF_TILED
     } else {
       return hipErrorInvalidValue;
     }

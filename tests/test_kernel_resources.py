@@ -1,4 +1,5 @@
-"""Compile-time resource checks of the staged multiply (no GPU needed).
+"""Compile-time resource checks of the staged multiply and the tiled kernels (no GPU
+needed).
 
 The staged multiply is written to keep its whole work-item state in
 registers: a spill to scratch memory there is written back once per work item
@@ -6,6 +7,7 @@ registers: a spill to scratch memory there is written back once per work item
 reload waits for every load in flight.  These checks compile the kernel for
 gfx950 and read the compiler's resource report."""
 
+import functools
 import os
 import re
 import shutil
@@ -18,18 +20,23 @@ CSRC = os.path.join(ROOT, "paper_2609_32259_amd", "csrc")
 HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
 
 
-def _resources(src, kernel, tmp_path):
-    if not os.path.exists(HIPCC):
-        pytest.skip("hipcc not available")
+@functools.lru_cache(maxsize=None)
+def _report(src):
     cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "--cuda-device-only", "-c",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}",
            "-Rpass-analysis=kernel-resource-usage", os.path.join(CSRC, src),
-           "-o", str(tmp_path / "k.o")]
+           "-o", os.devnull]
     out = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert out.returncode == 0, out.stdout[-2000:]
+    return out.stdout
+
+
+def _resources(src, kernel, tmp_path):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
     res, cur = {}, None
-    for line in out.stdout.splitlines():
+    for line in _report(src).splitlines():
         m = re.search(r"Function Name: (\S+)", line)
         if m:
             cur = m.group(1)
@@ -49,3 +56,15 @@ def test_staged_multiply_uses_no_scratch_and_fits_lds(tmp_path):
     assert r["VGPRs Spill"] == 0, r
     assert r["LDS Size"] <= 160 * 1024, r
     assert r["Occupancy"] >= 2, r   # two waves per SIMD: 8 waves in one workgroup per CU
+
+
+@pytest.mark.parametrize("args,scratch", [("ILi4ELb0ELb0ELb0", 0), ("ILi8ELb0ELb0ELb0", 60),
+                                          ("ILi2ELb0ELb1ELb0", 0), ("ILi8ELb1ELb1ELb0", 16)],
+                         ids=["4 heads, plain order", "8 heads, plain order", "2 heads",
+                              "8 heads, more than 8 sender heads"])
+def test_tiled_kernels_keep_their_registers(args, scratch, tmp_path):
+    # scratch bytes a lane: the work order's search or the rotations in flight must not
+    # push out registers that the multiply has to spare
+    r = _resources("transfer.hip", "transfer_bf16_tiled_kernel" + args, tmp_path)
+    assert r["ScratchSize"] <= scratch, r
+    assert r["Occupancy"] >= 2, r
