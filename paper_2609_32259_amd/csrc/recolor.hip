@@ -811,13 +811,13 @@ __global__ void info_kernel(const NsState* st, hf_recolor_info* info) {
 // The solve for p, q <= kSmallDim in two launches: one workgroup of 8 waves per
 // root iteration, then one for the rest.  Within a workgroup an iteration
 // ends when it has converged, where the launches of the general path
-// go on: a launch that finds nothing to do takes 4.4 us, and 220 of the 270 do.
-// 100 x 37: 0.97 ms, against 4.0 of one launch per product and 1.8 of the general path
-// below.
-// What bounds it: one CU's matrix cores and the latency of its loads; past 128
-// the products outgrow one CU.
+// go on, and most of them find nothing to do.
+// What bounds it: one CU's matrix cores and the latency of its loads.  us here and on
+// the general path: 32 x 32 267/1122, 64 x 64 521/1133, 96 x 48 872/1239, 100 x 37
+// 1063/1298, 96 x 96 1450/1635; 112 x 64 1341/1276, 112 x 112 2246/1728, 128 x 16
+// 1415/1128, 128 x 128 2785/1444: past about 104 the products outgrow one CU.
 // ---------------------------------------------------------------------------
-constexpr int kSmallDim = 128;
+constexpr int kSmallDim = 104;
 constexpr int kSmallThreads = 512;
 
 struct SmallProduct {
