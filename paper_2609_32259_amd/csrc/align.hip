@@ -8,7 +8,8 @@
 // writes its entries.  What bounds it is latency: the searches' chains of
 // loads (the three of a row advance together), and the launches, about 6 us each
 // whatever they do.  So:
-//   * up to kOneBlockRows rows: one workgroup does everything (align_one_kernel);
+//   * up to kOneBlockRows rows of a few sequences, unless they overlap many sender
+//     tokens (one_block): one workgroup does everything (align_one_kernel);
 //   * otherwise align_count writes each workgroup's totals, the counts and
 //     partners are parked in row_ptr / den, and align_fill sums the totals of the
 //     workgroups before its own.  Each receiver row is handled by the same thread
@@ -28,6 +29,7 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 constexpr int kOneBlockRows = 1024;
+constexpr int kOneBlockSeqs = 4;
 constexpr int kScanBlocks = 1024;
 
 // One binary search over a[0..n).
@@ -116,11 +118,15 @@ __device__ __forceinline__ RowInfo row_info(const AlignArgs& p, const int32_t* s
   // the last sender token ending at or before re; in overlap mode the first one
   // ending after rb and the first one starting at or after re
   Search past(se, Ts, rb < re), first(se, Ts, overlap), end(sb, Ts, overlap);
-  for (int n = Ts; n > 0; n >>= 1) {
-    const int v0 = past.probe(), v1 = first.probe(), v2 = end.probe();
-    past.advance(!(v0 > re));
-    first.advance(!(v1 > rb));
-    end.advance(!(v2 >= re));
+  if (overlap) {
+    for (int n = Ts; n > 0; n >>= 1) {
+      const int v0 = past.probe(), v1 = first.probe(), v2 = end.probe();
+      past.advance(!(v0 > re));
+      first.advance(!(v1 > rb));
+      end.advance(!(v2 >= re));
+    }
+  } else {
+    for (int n = Ts; n > 0; n >>= 1) past.advance(!(past.probe() > re));
   }
   if (rb < re) {
     int i = past.lo - 1;
@@ -188,15 +194,15 @@ __device__ int first_nonempty(const int32_t* sb, const int32_t* se, int Ts, long
 // The whole alignment of up to kOneBlockRows receiver rows, one per thread.
 __global__ __launch_bounds__(kOneBlockRows) void align_one_kernel(const AlignArgs p) {
   __shared__ long long red[kOneBlockRows / 64];
-  __shared__ int need[HF_MAX_BATCH];
-  __shared__ int first[HF_MAX_BATCH];
+  __shared__ int need[kOneBlockSeqs];
+  __shared__ int first[kOneBlockSeqs];
   const int g = threadIdx.x;
   const bool valid = g < p.total_rows;
   int b = 0;
   while (b + 1 < p.B && p.r0[b + 1] <= g) ++b;
   const int32_t* sb = p.s_beg + p.s0[b];
   const int32_t* se = p.s_end + p.s0[b];
-  if (g < HF_MAX_BATCH) need[g] = 0;
+  if (g < kOneBlockSeqs) need[g] = 0;
   RowInfo r{-1, 0, 0, 0};
   int rb = 0, re = 0;
   long long cnt = 0, part = -1;
@@ -339,9 +345,22 @@ size_t align_workspace_bytes(int nblk) {
   return 2 * up(n * sizeof(long long)) + 2 * up(n * sizeof(int32_t));
 }
 
+// Whether one workgroup aligns the batch.  It looks for a fallback one sequence after
+// the other: us of one workgroup and of two launches at 1,024 rows, 2 sequences
+// 13.8/17.3, 4 16.7/17.2, 6 22/17, 16 39/18, 64 124/21.  And it walks the overlaps on one
+// CU: 900 rows of 1, 9, 16 and 99 sender tokens each 13.6/17.5, 25/20, 49/30, 302/139;
+// 500 rows 13.9/17.3, 17/20, 31/30, 177/136.  Up to kAlignBlock rows the two launches
+// have no more than one workgroup a sequence either (250 rows of 98: 100/131).
+static bool one_block(const AlignArgs& a) {
+  if (a.total_rows < 1 || a.total_rows > kOneBlockRows || a.B > kOneBlockSeqs) return false;
+  const long long senders = a.s0[a.B - 1] + a.Ts[a.B - 1];
+  return a.mode == HF_ALIGN_TA || a.total_rows <= kAlignBlock ||
+         senders * a.total_rows <= 4LL << 20;
+}
+
 hipError_t launch_alignment(const AlignArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)a.nblk), block(kAlignBlock);
-  if (a.total_rows > 0 && a.total_rows <= kOneBlockRows) {
+  if (one_block(a)) {
     hipLaunchKernelGGL(align_one_kernel, dim3(1), dim3(kOneBlockRows), 0, s, a);
     return hipGetLastError();
   }

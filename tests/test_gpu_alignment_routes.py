@@ -1,5 +1,6 @@
-"""GPU alignment on each of its routes: one workgroup (up to 1024 rows), two
-launches, and three launches (past 1024 workgroups of 256 rows).  Small cases
+"""GPU alignment on each of its routes: one workgroup (up to 1024 rows of up to 4
+sequences that overlap few sender tokens), two launches, and three launches (past
+1024 workgroups of 256 rows).  Small cases
 against the oracle, bit for bit; the largest against the closed form of two
 tokenizations that tile one text (an entry per interval between neighbouring
 boundaries), as the oracle is a per-token loop."""
@@ -60,6 +61,25 @@ def test_alignment_around_the_one_workgroup_limit(hf, rows, mode):
         parts.append((sb, se, rb, re_))
     seg = synth.concat_segmentations(parts)
     print(f"[gpu-align] rows={rows} {mode}", flush=True)
+    exp = al.build_alignment_batched(seg.s_cu, seg.r_cu, seg.s_beg, seg.s_end, seg.r_beg, seg.r_end,
+                                     mode)
+    for g, e in zip(_run(hf, seg, mode), exp):
+        assert np.array_equal(g, e)
+
+
+# sequences, rows of each, sender tokens of each: both sides of 4 sequences, and of the
+# products of rows and sender tokens past 256 rows
+@pytest.mark.parametrize("mode", ["overlap", "ta"])
+@pytest.mark.parametrize("B,n,m", [(4, 60, 70), (5, 60, 70), (64, 16, 20), (1, 256, 20000),
+                                   (1, 257, 16320), (1, 257, 16321), (2, 512, 2048), (2, 512, 2049)])
+def test_alignment_around_the_one_workgroup_rule(hf, B, n, m, mode):
+    rng = np.random.default_rng(B * n + m)
+    parts = []
+    for _ in range(B):
+        chars = m + 5 * n  # tokens of 1 character or a few; most rows have no shared end
+        parts.append(_tokens(rng, chars, m) + _tokens(rng, chars, n))
+    seg = synth.concat_segmentations(parts)
+    print(f"[gpu-align] B={B} rows={n} senders={m} {mode}", flush=True)
     exp = al.build_alignment_batched(seg.s_cu, seg.r_cu, seg.s_beg, seg.s_end, seg.r_beg, seg.r_end,
                                      mode)
     for g, e in zip(_run(hf, seg, mode), exp):
