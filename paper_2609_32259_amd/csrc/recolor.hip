@@ -172,30 +172,51 @@ struct GemmBatch {
 
 typedef double double2_t __attribute__((ext_vector_type(2)));
 
-// Stage a kBK x 64 slice of an operand in registers, 4 elements per thread.
-// KM: stored k-major (element (i, kk) at P[kk * ld + i]), else row-major.
-// FAST: the slice lies inside the operand and its rows are 16-byte aligned.
+// One thread's 4 elements of each kBK x 64 slice of an operand: element (i, kk) at
+// P[kk ld + i] (KM) or P[i ld + kk].  FAST: the tile lies inside the operand and its
+// rows are 16-byte aligned.  Otherwise rows past the edge repeat the last one; what
+// they give is not stored.  Nothing looks at a loaded value before gemm_store: with
+// elements selected in every slice (each waits for its load) a 333 x 777 x 555 product
+// took 80 us and 2000 x 2000 x 2000 440 to 500, now 33 and 300; a last slice that k cuts
+// goes through gemm_tail.
 template <bool KM, bool FAST>
-__device__ inline void gemm_load(const double* P, long long ld, int rows, long long k, int i0,
-                                 long long k0, int tid, double (&r)[4]) {
-  const int i = KM ? i0 + (tid & 15) * 4 : i0 + (tid & 63);
-  const long long kk = KM ? k0 + (tid >> 4) : k0 + (tid >> 6) * 4;
-  if (FAST) {
-    const double* q = KM ? P + kk * ld + i : P + (long long)i * ld + kk;
-    const double2_t a = *reinterpret_cast<const double2_t*>(q);
-    const double2_t b = *reinterpret_cast<const double2_t*>(q + 2);
-    r[0] = a.x; r[1] = a.y; r[2] = b.x; r[3] = b.y;
-  } else {
-    // elements past the edge read the last one inside and count as zero: loads
-    // under a condition would be waited for one by one
+struct GemmSrc {
+  const double* q;  // this thread's elements of slice 0
+  int off[4];       // KM, not FAST: its columns
+
+  __device__ inline GemmSrc(const double* P, long long ld, int rows, int i0, int tid) {
+    const int i = KM ? i0 + (tid & 15) * 4 : i0 + (tid & 63);
+    if (KM) q = P + (tid >> 4) * ld + (FAST ? i : 0);
+    else q = P + (long long)(FAST ? i : min(i, rows - 1)) * ld + (tid >> 6) * 4;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int ie = KM ? i + e : i;
-      const long long ke = KM ? kk : kk + e;
-      const long long ic = ie < rows ? ie : rows - 1, kc = ke < k ? ke : k - 1;
-      const double v = KM ? P[kc * ld + ic] : P[ic * ld + kc];
-      r[e] = ie < rows && ke < k ? v : 0.0;
+    for (int e = 0; e < 4; ++e) off[e] = KM ? min(i + e, rows - 1) : e;
+  }
+  // FAST: of the rows `down` below
+  __device__ inline void load(long long ld, long long kt, double (&r)[4], int down = 0) const {
+    const double* z = q + (KM ? kt * kBK * ld + down : kt * kBK + down * ld);
+    if (FAST) {
+      const double2_t a = *reinterpret_cast<const double2_t*>(z);
+      const double2_t b = *reinterpret_cast<const double2_t*>(z + 2);
+      r[0] = a.x; r[1] = a.y; r[2] = b.x; r[3] = b.y;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = z[off[e]];
     }
+  }
+};
+
+// The same elements of a slice from k0 that reaches past k: inputs past the end read
+// the last one and count as zero.
+template <bool KM>
+__device__ inline void gemm_tail(const double* P, long long ld, int rows, long long k, int i0,
+                                 long long k0, int tid, double (&r)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = min(KM ? i0 + (tid & 15) * 4 + e : i0 + (tid & 63), rows - 1);
+    const long long kk = KM ? k0 + (tid >> 4) : k0 + (tid >> 6) * 4 + e;
+    const long long in = kk < k ? kk : k - 1;
+    const double v = KM ? P[in * ld + i] : P[(long long)i * ld + in];
+    r[e] = kk < k ? v : 0.0;
   }
 }
 
@@ -234,14 +255,18 @@ __device__ inline void gemm_tile(const GemmJob& g, const double* A, const double
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int li = lane & 15, lk = lane >> 4;
-  const long long nk = (g.k + kBK - 1) / kBK;
-  if (nk <= 0) return;
+  const long long nk = g.k / kBK;  // whole slices
   GemmRegs<BM> r[PF];
+  const GemmSrc<AK, FAST> srcA(A, g.lda, g.m, m0, tid);
+  const GemmSrc<AK, FAST> srcA1(A, g.lda, g.m, m0 + (BM > 64 ? 64 : 0), tid);
+  const GemmSrc<BK, FAST> srcB(B, g.ldb, g.n, n0, tid);
   auto load = [&](GemmRegs<BM>& z, long long kt) {
-#pragma unroll
-    for (int h = 0; h < BM / 64; ++h)
-      gemm_load<AK, FAST>(A, g.lda, g.m, g.k, m0 + 64 * h, kt * kBK, tid, z.a[h]);
-    gemm_load<BK, FAST>(B, g.ldb, g.n, g.k, n0, kt * kBK, tid, z.b);
+    srcA.load(g.lda, kt, z.a[0]);
+    if (BM > 64) {
+      if (FAST) srcA.load(g.lda, kt, z.a[BM / 64 - 1], 64);
+      else srcA1.load(g.lda, kt, z.a[BM / 64 - 1]);
+    }
+    srcB.load(g.ldb, kt, z.b);
   };
   auto store = [&](const GemmRegs<BM>& z, int buf) {
 #pragma unroll
@@ -264,46 +289,58 @@ __device__ inline void gemm_tile(const GemmJob& g, const double* A, const double
     }
   };
   // slice kt + PF loads into the registers that slice kt has left
-  load(r[0], 0);
-  store(r[0], 0);
-  if (PF == 2 && nk > 1) load(r[1], 1);
-  __syncthreads();
-  long long kt = 0;
-  if (PF == 1) {
-    for (; kt + 1 < nk; ++kt) {
-      load(r[0], kt + 1);
-      multiply((int)(kt & 1));
-      store(r[0], (int)((kt + 1) & 1));
-      __syncthreads();
-    }
-  } else {
-    for (; kt + 3 < nk; kt += 2) {
-      load(r[0], kt + 2);
-      multiply(0);
-      store(r[PF - 1], 1);
-      __syncthreads();
-      load(r[PF - 1], kt + 3);
-      multiply(1);
-      store(r[0], 0);
-      __syncthreads();
-    }
-    // at most three slices left: kt in LDS buffer 0, kt + 1 in r[1]
-    if (kt + 2 < nk) load(r[0], kt + 2);
-    if (kt + 1 < nk) {
-      multiply(0);
-      store(r[PF - 1], 1);
-      __syncthreads();
-      ++kt;
-      if (kt + 1 < nk) {
+  if (nk > 0) {
+    load(r[0], 0);
+    store(r[0], 0);
+    if (PF == 2 && nk > 1) load(r[1], 1);
+    __syncthreads();
+    long long kt = 0;
+    if (PF == 1) {
+      for (; kt + 1 < nk; ++kt) {
+        load(r[0], kt + 1);
+        multiply((int)(kt & 1));
+        store(r[0], (int)((kt + 1) & 1));
+        __syncthreads();
+      }
+    } else {
+      for (; kt + 3 < nk; kt += 2) {
+        load(r[0], kt + 2);
+        multiply(0);
+        store(r[PF - 1], 1);
+        __syncthreads();
+        load(r[PF - 1], kt + 3);
         multiply(1);
         store(r[0], 0);
         __syncthreads();
+      }
+      // at most three slices left: kt in LDS buffer 0, kt + 1 in r[1]
+      if (kt + 2 < nk) load(r[0], kt + 2);
+      if (kt + 1 < nk) {
+        multiply(0);
+        store(r[PF - 1], 1);
+        __syncthreads();
         ++kt;
+        if (kt + 1 < nk) {
+          multiply(1);
+          store(r[0], 0);
+          __syncthreads();
+          ++kt;
+        }
       }
     }
+    multiply((int)(kt & 1));
+    __syncthreads();
   }
-  multiply((int)(kt & 1));
-  __syncthreads();
+  if (!FAST && g.k % kBK != 0) {
+#pragma unroll
+    for (int h = 0; h < BM / 64; ++h)
+      gemm_tail<AK>(A, g.lda, g.m, g.k, m0 + 64 * h, nk * kBK, tid, r[0].a[h]);
+    gemm_tail<BK>(B, g.ldb, g.n, g.k, n0, nk * kBK, tid, r[0].b);
+    store(r[0], 0);
+    __syncthreads();
+    multiply(0);
+    __syncthreads();
+  }
 }
 
 // The fp64 products.  A launch runs the BM x 64 tiles of up to four products
@@ -315,8 +352,9 @@ __device__ inline void gemm_tile(const GemmJob& g, const double* A, const double
 // tiles that reach its upper triangle computed, and mirrored.
 //
 // What bounds it: the fp64 matrix cores (78.6 TFLOP/s; the library reaches 72).
-// A 3072 x 3072 product takes 1.10 ms (53 TFLOP/s; 1.30 ms with 64 x 64 tiles and
-// loads under conditions).  64 x 32 per wave reads 6 fragments from LDS for 8
+// A 3072 x 3072 product takes 0.97 to 1.10 ms from one card to another (53 to 60
+// TFLOP/s; on the same cards 1.09 to 1.30 ms with 64 x 64 tiles and loads under
+// conditions).  64 x 32 per wave reads 6 fragments from LDS for 8
 // matrix instructions (32 x 32: 4 for 4); 128 x 128 tiles would leave the 576
 // of them 0.75 of three rounds.  Three workgroups per CU (1.10 ms) hide
 // the loads and the barrier better than two (1.18).  A workgroup takes every
@@ -366,7 +404,8 @@ __device__ __forceinline__ void gemm_batch(const GemmBatch& gb) {
       if (fast) gemm_tile<BM, true, true, true>(g, A, B, m0, n0, L, acc);
       else gemm_tile<BM, true, true, false>(g, A, B, m0, n0, L, acc);
     } else if (g.a_kmajor) {
-      gemm_tile<BM, true, false, false>(g, A, B, m0, n0, L, acc);
+      if (fast) gemm_tile<BM, true, false, true>(g, A, B, m0, n0, L, acc);
+      else gemm_tile<BM, true, false, false>(g, A, B, m0, n0, L, acc);
     } else if (g.b_kmajor) {
       if (fast) gemm_tile<BM, false, true, true>(g, A, B, m0, n0, L, acc);
       else gemm_tile<BM, false, true, false>(g, A, B, m0, n0, L, acc);
