@@ -40,9 +40,13 @@ constexpr double kNsSwitch = 1e-3;
 constexpr int kNsExtra = 2;
 // Scaling of the steps (ns_update): the smallest singular value assumed at the
 // start, for the roots and for the polar factor, and the largest squared scale.
-// Roots: 3e-2 takes 10, 14, 25 and 36 steps at condition numbers 10, 1e4, 1e8 and
-// 1e12 (3e-3: 13, 13, 22, 34; plain: 11, 19, 30, 41).
-constexpr double kNsFloorRoot = 3e-2;
+// Roots: a low bound takes fewer steps where S is badly conditioned (13, 22, 34 against
+// 14, 25, 36 at condition numbers 1e4, 1e8, 1e12) and 13 instead of 10 where it is not.
+// The eigenvalues' mean square over their squared mean tells: kNsSpread comes out
+// at condition numbers of some 1e3 to 1e4 if they are spread evenly on a log scale.
+constexpr double kNsFloorAlike = 3e-2;
+constexpr double kNsFloorSpread = 3e-3;
+constexpr double kNsSpread = 4.0;
 constexpr double kNsFloorPolar = 1e-2;
 constexpr double kNsMaxScale2 = 2.25;
 constexpr int kNsRestart = 20;
@@ -718,16 +722,17 @@ struct NsProblem {
   double* Z1;       // the second iterate's other factor
   NsState* st;
   double* partial;
-  double floor;     // singular value the scaling starts from
+  double* trace;    // trace of M + lam I (nullptr: the polar iteration)
 };
 struct NsPair {
   NsProblem q[2];
 };
 
-// The singular value the scaled steps start from: `floor`, or what the ridge
-// (relative to the norm) assures where that is more.
-__device__ inline double ns_start_bound(double floor, double ridge) {
-  return fmin(1.0, fmax(floor, sqrt(fmax(0.0, ridge))));
+// The singular value the scaled steps of a root start from: by the spread of the d
+// eigenvalues of S, or what the ridge assures where that is more.  c = |S|_F.
+__device__ inline double ns_root_bound(int d, double trace, double c, double lam) {
+  const double floor = d * c * c >= kNsSpread * trace * trace ? kNsFloorSpread : kNsFloorAlike;
+  return fmin(1.0, fmax(floor, sqrt(fmax(0.0, lam / c))));
 }
 
 __device__ inline NsState ns_initial(double again) {
@@ -754,6 +759,7 @@ __global__ __launch_bounds__(kRedThreads) void ns_start_kernel(const NsPair pr, 
   s = block_sum(s, red);
   if (threadIdx.x != 0) return;
   *q.lam = ridge * s / q.rows;
+  *q.trace = s + ridge * s;
   *q.st = ns_initial(1.0);
   if (blockIdx.x == 0) *polar = ns_initial(kNsFloorPolar);
 }
@@ -777,7 +783,7 @@ __global__ __launch_bounds__(kRedThreads) void ns_norm_kernel(const NsPair pr) {
   const double c = sqrt(sum_partials(q.partial, gridDim.x, red));
   if (threadIdx.x == 0) {
     *q.norm = c;
-    q.st->low = ns_start_bound(q.floor, add / c);
+    q.st->low = q.trace ? ns_root_bound(q.rows, *q.trace, c, add) : kNsFloorPolar;
   }
 }
 
@@ -852,11 +858,12 @@ __global__ void info_kernel(const NsState* st, hf_recolor_info* info) {
 // ends when it has converged, where the launches of the general path
 // go on, and most of them find nothing to do.
 // What bounds it: one CU's matrix cores and the latency of its loads.  us here and on
-// the general path: 32 x 32 267/1122, 64 x 64 521/1133, 96 x 48 872/1239, 100 x 37
-// 1063/1298, 96 x 96 1450/1635; 112 x 64 1341/1276, 112 x 112 2246/1728, 128 x 16
-// 1415/1128, 128 x 128 2785/1444: past about 104 the products outgrow one CU.
+// the general path: 32 x 32 265/1033, 64 x 64 520/1134, 80 x 80 1151/1250, 96 x 16
+// 765/994, 96 x 48 877/1055; 96 x 96 1449/1320, 100 x 37 with 10 steps 1064/1106, with 13
+// 1358/1227, 104 x 104 1924/1413, 128 x 16 1398/1048, 128 x 128 2779/1443: past 96 the
+// products outgrow one CU.
 // ---------------------------------------------------------------------------
-constexpr int kSmallDim = 104;
+constexpr int kSmallDim = 96;
 constexpr int kSmallThreads = 512;
 
 struct SmallProduct {
@@ -1011,7 +1018,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_roots_kernel(const NsPair
   };
   double s = 0.0;
   for (int i = tid; i < d; i += kSmallThreads) s += q.M[i * q.ld + i];
-  const double lam = ridge * total(s) / d;
+  const double trace = total(s), lam = ridge * trace / d;
   s = 0.0;
   for (int e = tid; e < d * d; e += kSmallThreads) {
     const int i = e / d, j = e - i * d;
@@ -1032,7 +1039,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_roots_kernel(const NsPair
     *q.lam = lam;
     *q.norm = c;
     st = ns_initial(1.0);
-    st.low = ns_start_bound(q.floor, lam / c);
+    st.low = ns_root_bound(d, trace + ridge * trace, c, lam);
     ns_update(&st, res);
   }
   __syncthreads();
@@ -1121,7 +1128,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_rest_kernel(const SmallRe
   for (int e = tid; e < p * q; e += kSmallThreads) w.X[0][e] *= inv;
   if (tid == 0) {
     st = ns_initial(kNsFloorPolar);
-    st.low = ns_start_bound(kNsFloorPolar, 0.0);
+    st.low = kNsFloorPolar;
   }
   __syncthreads();
   const bool tall = p >= q;
@@ -1489,7 +1496,6 @@ hipError_t ns_polar(int p, int q, double* X[2], double* P, double* partial, doub
   pr.q[0].norm = nrm;
   pr.q[0].st = st;
   pr.q[0].partial = partial;
-  pr.q[0].floor = kNsFloorPolar;
   hipLaunchKernelGGL(ns_norm_kernel, dim3((unsigned)grid_for(pq, kRedThreads, kMaxRedBlocks), 1),
                      dim3(kRedThreads), 0, s, pr);
   HF_CHECK(hipGetLastError());
@@ -1523,7 +1529,7 @@ hipError_t ns_polar(int p, int q, double* X[2], double* P, double* partial, doub
 }
 
 // Scalar slots of the solve's workspace.
-enum { kScLamZ = 0, kScLamY = 1, kScCZ = 2, kScCY = 3, kScNormM = 4, kScCount = 16 };
+enum { kScLamZ = 0, kScLamY = 1, kScCZ = 2, kScCY = 3, kScNormM = 4, kScTrZ = 5, kScTrY = 6, kScCount = 16 };
 
 }  // namespace
 
@@ -1728,7 +1734,7 @@ hipError_t launch_recolor_solve(int p, int q, const double* mu, const double* co
     n.Y = rb[i].Y[0];
     n.Z1 = rb[i].Z[1];
     n.st = st + i;
-    n.floor = kNsFloorRoot;
+    n.trace = sc + (i ? kScTrY : kScTrZ);
   }
   double* Xp[2] = {cv.take<double>((size_t)p * q), cv.take<double>((size_t)p * q)};
   const size_t e = p < q ? p : q;

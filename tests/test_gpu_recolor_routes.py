@@ -1,5 +1,5 @@
 """GPU parity of the offline construction where its kernels change route: the
-one-workgroup solve up to 104 features and the launch-per-product solve past
+one-workgroup solve up to 96 features and the launch-per-product solve past
 it, iterations long enough to restart their scaling, products on and off the
 16-byte tile path, and covariance tiles at their edges.  Tolerances as in
 test_gpu_recolor: 4 k eps for products and moments, 1e-8 for the solve."""
@@ -36,7 +36,7 @@ def _np(t):
 
 
 @pytest.mark.parametrize("p,q", [(128, 128), (129, 20), (20, 129), (33, 32), (16, 17), (260, 130),
-                                 (104, 104), (105, 20), (20, 105)])
+                                 (96, 96), (97, 20), (20, 97)])
 def test_solve_on_both_sides_of_the_one_workgroup_limit(hf, p, q):
     from paper_2609_32259_amd import synth
     cfg = synth.CalibConfig("route", n=3000, p=p, q=q)
