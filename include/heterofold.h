@@ -317,8 +317,8 @@ size_t hf_transfer_staged_workspace_bytes(int32_t B, const int32_t* s_len, const
  * cores with fp32 accumulation, adds bias and rotates in fp32, and rounds the
  * result once to bf16.
  * Supported by this library: d_h == 128 for HF_BF16 with receiver H in
- * {2, 4, 8} and one (layer, role) map under 2 GiB; any even d_h and H for
- * HF_F32 (d_in <= 4096).  Other valid shapes -- bf16 with d_h == 64 among
+ * {2, 4, 8} and one (layer, role) map under 2 GiB; any H and any d_h that is a
+ * multiple of 4 (rows of whole 16 bytes) for HF_F32 (d_in <= 4096).  Other valid shapes -- bf16 with d_h == 64 among
  * them -- return HF_ERR_UNSUPPORTED before anything is launched.
  * Receiver rows past r_len are not written.
  */
@@ -417,7 +417,8 @@ int32_t hf_transfer_kv_taps(int32_t B, const int32_t* s_len, const int32_t* r_le
  *   dtype      HF_F32 or HF_BF16: storage of x and y.
  *   x          device [n][ldx], row n holds x_n in its first p entries (ldx >= p).
  *   y          device [n][ldy], y_n in the first q entries (ldy >= q).
- *   w          device fp32 [n] sample weights (>= 0, positive sum), or NULL for 1.
+ *   w          device fp32 [n] sample weights (>= 0, positive sum), or NULL for 1;
+ *              a sample of weight 0 must be finite as well.
  *   r          device fp64 [1]: r = sqrt(sum w |x|^2 / (p sum w)).
  *   mu         device fp64 [p + q]: weighted means of z = x / r, then of y.
  *   cov        device fp64 [(p + q)^2] row-major: the joint covariance of

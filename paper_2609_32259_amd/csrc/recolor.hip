@@ -611,7 +611,8 @@ __global__ __launch_bounds__(256, 2) void cov_kernel(CovArgs g) {
       for (int e = 0; e < 4; ++e) {
         d[e] = (double)v[o][e] - sh[o][e];
         if (o < 2) d[e] *= wd;
-        // rows of weight 0 count as absent whatever they hold
+        // rows past the range count as zero, rows of weight 0 as absent if finite (an
+        // Inf or NaN sample reaches the result whatever its weight, here and in the means)
         if (!in || (o >= 2 && wr == 0.f)) d[e] = 0.0;
       }
       double* q = (o < 2 ? As : Bs)[buf][kk] + (o & 1) * 64 + c4;

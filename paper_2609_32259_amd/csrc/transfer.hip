@@ -224,12 +224,13 @@ __device__ __forceinline__ void scale_by_weights(float (*y)[16], const int* feat
 }
 
 // ---------------------------------------------------------------------------
-// bf16 transfer kernel, tiled (d_h = 128, up to 8 sender heads; NTW = 4 for 8
-// receiver heads, NTW = 2 for 4).
+// bf16 transfer kernel, tiled (d_h = 128; 2, 4 or 8 receiver heads; X holds up to 8
+// sender heads, more take a pass per group of 8).
 //
 // One workgroup = 8 waves computes 64 receiver rows x all d_r receiver
 // features of one (layer, role), in three phases after copying the tile's
-// staging record (stage_tiles_kernel) into LDS:
+// staging record (written by prologue_kernel) into LDS, or staging it there
+// itself (OWN):
 //   build: all 512 threads form the whole aligned feature block X[64][d_in]
 //          in fp32 -- gather the tile's CSR entries (from the record), mix the
 //          two sender-layer taps, un-rotate keys, weight and sum -- and store
@@ -240,18 +241,20 @@ __device__ __forceinline__ void scale_by_weights(float (*y)[16], const int* feat
 //   mma:   each wave multiplies its output tiles by X over all d_in/16 k-steps
 //          (v_mfma_f32_32x32x16_bf16: packed map fragment from global memory as
 //          A, X from LDS as B) with a four-deep register prefetch of the map
-//          fragments and no barrier inside the loop.  Workgroups start the loop
-//          at different sender heads so that concurrent workgroups stream
-//          different parts of the map.
+//          fragments and no barrier inside the loop.  In plain work order
+//          workgroups start the loop at different sender heads so that
+//          concurrent workgroups stream different parts of the map.
 //   store: the tile's receiver RoPE rows and the bias are copied into LDS
 //          once; bias, rotation and bf16 rounding, then staged row writes.
-// Wave w owns NTW 32-feature tiles of one receiver head (NTW = 4: the whole
-// head w; NTW = 2: tiles {w%2, w%2 + 2} of head w/2), so RoPE pairs
+// Wave w owns 32-feature tiles of one receiver head: with 8 heads all four tiles
+// of head w, with 4 heads tiles {w%2, w%2 + 2} of head w/2, with 2 heads tiles
+// {w/2%2, w/2%2 + 2} of head w/4 for the 32 rows from 32 (w%2) on.  So RoPE pairs
 // (f, f + 64) stay inside a lane; the accumulator of lane l, row block mt,
-// tile q, register i holds receiver row 32 mt + l%32 and feature
-// feat[q] + 8 (i/4) + 4 (l/32) + i%4.
+// tile q, register i holds receiver row 32 mt + l%32 (of the wave's rows) and
+// feature feat[q] + 8 (i/4) + 4 (l/32) + i%4.
 //
-// The un-rotation of sender row i at position p_i is split as
+// Where the tile's record is prepared (4 or 8 receiver heads, up to 8 sender
+// heads), the un-rotation of sender row i at position p_i is split as
 // U(p_i) = U(q_g) U(p_i - q_g) with q_g the position of the smallest sender
 // token of the lane group's run: the small-offset rotations U(0..15) sit in
 // LDS and U(q_g) is applied once to each row's sum.  Tiles whose entry count or
@@ -267,8 +270,8 @@ constexpr int kDtBytes = kDMax * kDH * 4;            // U(delta) rows: cos | sin
 constexpr int kOffDt = kXBytes;
 constexpr int kOffEnt = kOffDt + kDtBytes;
 // Staged tile record: estart, gbase, ecol, ew, einfo, flags, gstart, row min /
-// max sender index; written once per row tile by the staging kernel and copied
-// whole into LDS by every (layer, role) of the tile.
+// max sender index; written once per row tile by the prologue and copied whole
+// into LDS by every (layer, role) of the tile.
 constexpr int kEntInts = 65 + 64 + kEMax * 3 + 4 + 65 + 2 * 64;
 constexpr int kRecBytes = 8192;  // 8 waves x 64 lanes x 16 bytes
 static_assert(kEntInts * 4 <= kRecBytes, "tile record size");
@@ -1116,8 +1119,9 @@ size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h) {
 
 // In queues up to kQueueTiles row tiles, in plain order past that.  In plain order the
 // tiles of a (layer, role) lie on all XCDs and each fetches the map (2 MB for 8 -> 8
-// heads, half that for 8 -> 4 and 4 -> 8).  Queued over plain kernel time at 3, 7, 14,
-// 28, 56, 78, 100, 125, 167 and 223 tiles (200 to 16K tokens):
+// heads, half that for 8 -> 4 and 4 -> 8): 577, 1130 and 1905 MB fetched at 3, 7 and 14
+// tiles for 168 MB of maps, and 249, 403 and 627 MB in queues.  Queued over plain
+// kernel time at 3, 7, 14, 28, 56, 78, 100, 125, 167 and 223 tiles (200 to 16K tokens):
 //   8 -> 8         .59 .69 .76 .81 .93 .97 .99 .98 1.00 1.00  (93 -> 55 us at 3 tiles)
 //   8 -> 4         .74 .71 .90 .96 1.00 .98 1.00 .98 1.00 .99
 //   4 -> 8         .70 .71 .86 .94 1.00 1.00 1.03 .99 1.01 1.01

@@ -1,5 +1,5 @@
 // fp32 transfer kernels: the definitions of the bf16 kernels (transfer.hip)
-// with fp32 operands, fp32 sums throughout, and any even head size.
+// with fp32 operands, fp32 sums throughout, and head sizes that are multiples of 4.
 #include <hip/hip_runtime.h>
 
 #include "hf_device.h"
@@ -27,8 +27,8 @@ constexpr int kF32Threads = 256;
 //
 // What bounds it: at 24 -> 28 layers, 4 -> 2 heads of 64, 1,778 receiver rows,
 // the products take 42 us at the 157 TFLOP/s of the fp32 matrix cores and the
-// caches 33 us of memory traffic; the kernel takes 127 us there, of which 51
-// are left without the products and 32 without the sender rows too.  One
+// caches 33 us of memory traffic; the kernel takes 127 us there, 72 without the
+// products and their map loads, 41 without the sender rows too.  One
 // scalar FMA per two loads, with the map read down its columns and every
 // feature behind a chain of three dependent loads (the kernel for larger heads
 // below), takes 965 us.  On 340 -> 301 tokens, 4 -> 6 layers, 2 heads of 64:

@@ -115,7 +115,7 @@ def test_token_major_against_the_oracle(torch, staged):
 
 
 def test_fp32_layouts(torch):
-    """The fp32 kernel (any even d_h; here 64) through the same strides."""
+    """The fp32 kernel (head sizes that are multiples of 4; here 64) through the same strides."""
     cfg = synth.TINY_F32.with_(name="fp32 layouts", batch=2)
     wl = synth.make_workload(cfg, seed=62, device="cuda")
     T_cap = int(wl.seg.r_len.max()) + 2
