@@ -75,7 +75,7 @@ def kernel_name(cfg, r_len):
     records = cfg.H_r in (4, 8) and cfg.H_s <= 8
     tf = lambda b: "true" if b else "false"  # noqa: E731
     multi = cfg.n_taps > 1 or cfg.H_s > 8
-    queued = records and not multi and sum(-(-int(t) // 64) for t in r_len) <= 128
+    queued = records and not multi and sum(-(-int(t) // 64) for t in r_len) <= 96
     return (f"transfer_bf16_tiled_kernel<{cfg.H_r}, {tf(multi)}, {tf(not records)}, "
             f"{tf(queued)}>")
 

@@ -1137,9 +1137,11 @@ size_t transfer_tile_record_bytes(int dtype, int H_r, int H_s, int d_h) {
 //   8 -> 4, 3 taps .74 .60 .81 .99 .99 1.00 1.03 1.00 1.00 .98
 //   8 -> 2         .96 .89 .97 1.02 1.01 1.00 1.01 1.00 1.02 1.01
 //   16 -> 8        .76 .63 .78 .90 .95 .97
-// so the line lies where the largest map stops gaining; runs differ by 1 to 2%.
+// Runs differ by 1 to 2%.  On a second card whole calls of 8 -> 8 heads at 89, 100, 114
+// and 125 tiles .97 .99 1.00 .98, of 4 -> 8 1.00 1.02 1.02 1.00, of 8 -> 4 .98 1.00 1.01
+// .99; on a third 8 -> 8 at 115 tiles 1.03.  So the line lies where no shape loses.
 // A kernel of one item per workgroup needs queues of one length.
-constexpr int kQueueTiles = 128;
+constexpr int kQueueTiles = 96;
 
 void transfer_order(TransferArgs& a) {
   const bool one_each = a.concat || a.H_s > kHMax || !uses_records(HF_BF16, a.H_r, a.H_s, a.d_h);

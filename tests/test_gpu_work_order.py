@@ -1,5 +1,5 @@
-"""GPU: the tiled kernel's work items dealt in queues (one per XCD up to 128 row
-tiles, one past that): queues of different lengths with more items than
+"""GPU: the tiled kernel's work items dealt in queues (one per XCD up to 96 row
+tiles, plain order past that): queues of different lengths with more items than
 workgroups, fewer (layer, role)s than queues, one item per workgroup, and both
 sides of the limit; every layer and role against the fp64 oracle on windows of
 rows, and no row past the end touched."""
@@ -27,8 +27,10 @@ def torch():
 SHAPES = [(8, 8, 9, 2500, "interp2"),       # 18 maps in 8 queues, 720 items
           (8, 4, 9, 2500, "interp2"),
           (4, 8, 3, 6000, "interp2"),       # 6 maps: two queues empty, 564 items
-          (8, 8, 1, 128 * 64, "interp2"),   # 128 tiles: 2 queues hold all 256 items
-          (8, 8, 1, 128 * 64 + 1, "interp2"),  # 129 tiles: plain order
+          (8, 8, 1, 96 * 64, "interp2"),    # 96 tiles: 2 queues hold all 192 items
+          (8, 8, 1, 96 * 64 + 1, "interp2"),   # 97 tiles: plain order
+          (8, 8, 1, 128 * 64, "interp2"),
+          (8, 8, 1, 128 * 64 + 1, "interp2"),  # more items than workgroups
           (8, 8, 5, 60, "interp2"),         # 10 items, one each
           (8, 2, 9, 700, "interp2"),        # one item per workgroup, uneven: plain order
           (8, 2, 4, 700, "interp2"),        # one item per workgroup, even: queues
