@@ -27,6 +27,7 @@ constexpr int kBN = 64, kBK = 16;  // a tile is 128 x 64 or 64 x 64
 constexpr int kPad = 4;            // padding of the LDS rows, doubles
 constexpr int kGemmThreads = 256;
 constexpr int kGemmResident = 768;  // workgroups resident at once (3 per CU: 51 KB of LDS each)
+constexpr int kGemmResidentShort = 1024;  // of the kernel for short products (4 per CU)
 // Products with fewer 128 x 64 tiles than this (two per CU) run on 64 x 64 tiles.
 constexpr int kGemmSmallTiles = 512;
 constexpr int kRedThreads = 256;
@@ -251,11 +252,11 @@ struct GemmRegs {
 
 // The k-loop of one tile, for one pair of layouts.  PF slices load while one is
 // multiplied: one for the tall tile, whose three workgroups per CU hide each
-// other's loads, two for the small one, which runs where a CU has one workgroup.
-template <int BM, bool AK, bool BK, bool FAST>
+// other's loads, two for the small one, which runs where a CU has one workgroup;
+// one again for short products on small tiles (Batch::launch).
+template <int BM, int PF, bool AK, bool BK, bool FAST>
 __device__ inline void gemm_tile(const GemmJob& g, const double* A, const double* B, int m0, int n0,
                                  GemmLds<BM>& L, double4_t (&acc)[BM / 32][2]) {
-  constexpr int PF = BM == 64 ? 2 : 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int li = lane & 15, lk = lane >> 4;
@@ -364,7 +365,7 @@ __device__ inline void gemm_tile(const GemmJob& g, const double* A, const double
 // the loads and the barrier better than two (1.18).  A workgroup takes every
 // gridDim.x-th tile, so the launches of an iteration that is already done are
 // 768 workgroups and not thousands.
-template <int BM>
+template <int BM, int PF>
 __device__ __forceinline__ void gemm_batch(const GemmBatch& gb) {
   __shared__ GemmLds<BM> L;
   __shared__ double red[kGemmThreads / 64];
@@ -405,17 +406,17 @@ __device__ __forceinline__ void gemm_batch(const GemmBatch& gb) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) acc[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
     if (g.a_kmajor && g.b_kmajor) {
-      if (fast) gemm_tile<BM, true, true, true>(g, A, B, m0, n0, L, acc);
-      else gemm_tile<BM, true, true, false>(g, A, B, m0, n0, L, acc);
+      if (fast) gemm_tile<BM, PF, true, true, true>(g, A, B, m0, n0, L, acc);
+      else gemm_tile<BM, PF, true, true, false>(g, A, B, m0, n0, L, acc);
     } else if (g.a_kmajor) {
-      if (fast) gemm_tile<BM, true, false, true>(g, A, B, m0, n0, L, acc);
-      else gemm_tile<BM, true, false, false>(g, A, B, m0, n0, L, acc);
+      if (fast) gemm_tile<BM, PF, true, false, true>(g, A, B, m0, n0, L, acc);
+      else gemm_tile<BM, PF, true, false, false>(g, A, B, m0, n0, L, acc);
     } else if (g.b_kmajor) {
-      if (fast) gemm_tile<BM, false, true, true>(g, A, B, m0, n0, L, acc);
-      else gemm_tile<BM, false, true, false>(g, A, B, m0, n0, L, acc);
+      if (fast) gemm_tile<BM, PF, false, true, true>(g, A, B, m0, n0, L, acc);
+      else gemm_tile<BM, PF, false, true, false>(g, A, B, m0, n0, L, acc);
     } else {
-      if (fast) gemm_tile<BM, false, false, true>(g, A, B, m0, n0, L, acc);
-      else gemm_tile<BM, false, false, false>(g, A, B, m0, n0, L, acc);
+      if (fast) gemm_tile<BM, PF, false, false, true>(g, A, B, m0, n0, L, acc);
+      else gemm_tile<BM, PF, false, false, false>(g, A, B, m0, n0, L, acc);
     }
 
     double alpha = g.alpha, beta = g.beta;
@@ -455,9 +456,10 @@ __device__ __forceinline__ void gemm_batch(const GemmBatch& gb) {
   }
 }
 
-template <int BM>
-__global__ __launch_bounds__(kGemmThreads, 3) void gemm_f64_kernel(const GemmBatch gb) {
-  gemm_batch<BM>(gb);
+template <int BM, int PF>
+__global__ __launch_bounds__(kGemmThreads, BM == 64 && PF == 1 ? 4 : 3) void gemm_f64_kernel(
+    const GemmBatch gb) {
+  gemm_batch<BM, PF>(gb);
 }
 
 // The products of one step of an iteration, described once in the workspace:
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f64_kernel(const GemmBat
 template <int BM>
 __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f64_planned_kernel(
     const GemmBatch* __restrict__ gb) {
-  gemm_batch<BM>(*gb);
+  gemm_batch<BM, BM == 64 ? 2 : 1>(*gb);
 }
 
 constexpr int kPlanPart = 4;  // descriptions per launch of the kernel that stores them
@@ -1311,19 +1313,37 @@ struct Batch {
     ++g.n_jobs;
     return j;
   }
+  // Numbers the tiles of height bm.
+  long long number(int bm) {
+    g.bm = bm;
+    for (int i = 0; i < g.n_jobs; ++i) g.first[i + 1] = g.first[i] + tiles_of(g.job[i], bm);
+    return g.first[g.n_jobs];
+  }
   // Chooses the tile and numbers the tiles.
   long long cut() {
-    for (g.bm = 128;; g.bm = 64) {
-      for (int i = 0; i < g.n_jobs; ++i) g.first[i + 1] = g.first[i] + tiles_of(g.job[i], g.bm);
-      if (g.bm == 64 || g.first[g.n_jobs] >= kGemmSmallTiles) return g.first[g.n_jobs];
-    }
+    const long long tall = number(128);
+    return tall >= kGemmSmallTiles ? tall : number(64);
   }
+  // A short product's tiles are mostly staging and stores: small tiles with one slice
+  // in flight, of which four instead of three workgroups fit a CU, also where three
+  // a CU would leave a nearly empty last wave.  us that way and otherwise, k = 16, 64,
+  // 256: 50000 x 64 12/15, 19/22, 43/45; 2600 x 2600 18/22, 29/35, 72/84.  With fewer
+  // tiles, or many waves, k = 256 is better off with the others: 640 x 640 18.2/17.4,
+  // 4096 x 4096 157/152; k = 64 there 58/58, 8192 x 4096 111/110.
   hipError_t launch(hipStream_t s) {
+    const long long k = g.n_jobs == 1 ? g.job[0].k : INT64_MAX;
+    const long long small = number(64);
+    if (k <= 64 || (k <= 256 && small > kGemmResident && small < 2048)) {
+      if (small <= 0) return hipSuccess;
+      const dim3 grid((unsigned)std::min<long long>(small, kGemmResidentShort));
+      hipLaunchKernelGGL((gemm_f64_kernel<64, 1>), grid, dim3(kGemmThreads), 0, s, g);
+      return hipGetLastError();
+    }
     const long long tiles = cut();
     if (tiles <= 0) return hipSuccess;
-    const dim3 grid((unsigned)(tiles < kGemmResident ? tiles : kGemmResident));
-    if (g.bm == 128) hipLaunchKernelGGL(gemm_f64_kernel<128>, grid, dim3(kGemmThreads), 0, s, g);
-    else hipLaunchKernelGGL(gemm_f64_kernel<64>, grid, dim3(kGemmThreads), 0, s, g);
+    const dim3 grid((unsigned)std::min<long long>(tiles, kGemmResident));
+    if (g.bm == 128) hipLaunchKernelGGL((gemm_f64_kernel<128, 1>), grid, dim3(kGemmThreads), 0, s, g);
+    else hipLaunchKernelGGL((gemm_f64_kernel<64, 2>), grid, dim3(kGemmThreads), 0, s, g);
     return hipGetLastError();
   }
 };

@@ -133,7 +133,10 @@ def test_polar_iteration_restarts_its_scaling(hf, p, q):
 
 @pytest.mark.parametrize("ak,bk", [(False, True), (True, True), (False, False), (True, False)])
 @pytest.mark.parametrize("m,n,k", [(256, 128, 64), (129, 65, 48), (127, 63, 15), (300, 200, 33),
-                                   (8200, 520, 40)])  # the last: tall tiles, 8 rows in the lowest
+                                   # tall tiles with 8 rows in the lowest; more tiles than
+                                   # resident workgroups, short and just past it
+                                   (8200, 520, 260), (8200, 520, 40), (2100, 2110, 17),
+                                   (2600, 1000, 256), (2600, 1000, 257)])
 def test_gemm_tile_edges(hf, ak, bk, m, n, k):
     rng = np.random.default_rng(m + n + k)
     opA, opB = rng.standard_normal((m, k)), rng.standard_normal((k, n))
