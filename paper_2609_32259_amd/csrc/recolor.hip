@@ -27,7 +27,6 @@ constexpr int kBN = 64, kBK = 16;  // a tile is 128 x 64 or 64 x 64
 constexpr int kPad = 4;            // padding of the LDS rows, doubles
 constexpr int kGemmThreads = 256;
 constexpr int kGemmResident = 768;  // workgroups resident at once (3 per CU: 51 KB of LDS each)
-constexpr int kGemmResidentShort = 1024;  // of the kernel for short products (4 per CU)
 // Products with fewer 128 x 64 tiles than this (two per CU) run on 64 x 64 tiles.
 constexpr int kGemmSmallTiles = 512;
 constexpr int kRedThreads = 256;
@@ -1327,15 +1326,17 @@ struct Batch {
   // A short product's tiles are mostly staging and stores: small tiles with one slice
   // in flight, of which four instead of three workgroups fit a CU, also where three
   // a CU would leave a nearly empty last wave.  us that way and otherwise, k = 16, 64,
-  // 256: 50000 x 64 12/15, 19/22, 43/45; 2600 x 2600 18/22, 29/35, 72/84.  With fewer
-  // tiles, or many waves, k = 256 is better off with the others: 640 x 640 18.2/17.4,
-  // 4096 x 4096 157/152; k = 64 there 58/58, 8192 x 4096 111/110.
+  // 256: 50000 x 64 12/15, 19/22, 43/45; 2600 x 2600 18/22, 29/35, 72/84; 4096 x 4096
+  // 32/33, 55/58.  With fewer tiles, or many waves, k = 256 is better off with the
+  // others: 640 x 640 18.2/17.4, 4096 x 4096 157/152.  A workgroup per tile, so that
+  // one's stores run beside the next one's loads: 8192 x 4096, k = 64 106, resident
+  // workgroups 111.
   hipError_t launch(hipStream_t s) {
     const long long k = g.n_jobs == 1 ? g.job[0].k : INT64_MAX;
     const long long small = number(64);
     if (k <= 64 || (k <= 256 && small > kGemmResident && small < 2048)) {
       if (small <= 0) return hipSuccess;
-      const dim3 grid((unsigned)std::min<long long>(small, kGemmResidentShort));
+      const dim3 grid((unsigned)std::min<long long>(small, 1 << 20));
       hipLaunchKernelGGL((gemm_f64_kernel<64, 1>), grid, dim3(kGemmThreads), 0, s, g);
       return hipGetLastError();
     }
